@@ -407,7 +407,11 @@ dresd_status dresd_ivf_search_next_token(dresd_ivf *ivf, const float *queries,
  *   inner product (fp32 accumulation of exact products).
  *   x device [n, d] row-major in dtype; 0 <= n <= DRESD_N_MAX (0: no-op);
  *   1 <= d <= 16384; centroids device [P, d] fp32, 1 <= P <= DRESD_PARTS_MAX;
- *   assign device [n] int32 out; score device [n] fp32 out.
+ *   assign device [n] int32 out; score device [n] fp32 out.  Rows of at most
+ *   256 dims are multiplied on the 16-bit matrix cores (the centroids split
+ *   into three exact parts) with a workspace of about 6 P d bytes (at most
+ *   256 MiB; 8 n more for small n) per (device, stream), kept as for
+ *   dresd_kmeans_update; a call that cannot get one runs without.
  * dresd_kmeans_update: each centroid becomes the unit vector along the sum of
  *   the rows assigned to it; a centroid with no rows (or a zero sum) is left
  *   as it is.  Sums are exact to 2^-30 per element and independent of the

@@ -9,7 +9,9 @@
 //            64 rows (decoded from their storage type, staged once when they
 //            have at most 128 dims) and walks all centroids in tiles of 64 x
 //            128 dims, loading the next tile while it multiplies this one; the
-//            argmax is fused into the epilogue of each centroid tile.
+//            argmax is fused into the epilogue of each centroid tile.  Rows
+//            of at most 256 dims run on the 16-bit matrix cores instead
+//            (dresd_assign.hip); this kernel then computes the rows left to it.
 //   update : each centroid becomes the unit vector along the sum of its
 //            rows (unchanged when it has none).  Rows are added into 64-bit
 //            fixed point (2^-30 units) with integer atomics, so the sums, and
@@ -104,11 +106,29 @@ __global__ void __launch_bounds__(256) dresd_kmeans_assign(KmeansParams p) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, m = lane & 15;
-  const int64_t r0 = (int64_t)blockIdx.x * kKR;
   const int d = p.d, P = p.P;
   const int es = DT == kF32 ? 4 : 2;
   const bool xvec = (((uintptr_t)p.x & 15u) == 0) && ((d * es) % 16 == 0);
   const bool cvec = (((uintptr_t)p.centroids & 15u) == 0) && (d % 4 == 0);
+  const int64_t nblk = (p.n + kKR - 1) / kKR;
+  for (int64_t rb = blockIdx.x; rb < nblk; rb += gridDim.x) {
+  const int64_t r0 = rb * kKR;
+  if (p.only_left) {
+    // rows the 16-bit path has done (unpacking its results); the rest stay
+    bool left = false;
+    if (tid < kKR && r0 + tid < p.n) {
+      const int64_t row = r0 + tid;
+      if (p.packed) {
+        const uint64_t key = p.packed[row];
+        left = key == ~0ull;
+        p.assign[row] = left ? -1 : (int32_t)~(uint32_t)key;
+        if (p.score && !left) p.score[row] = order_value((uint32_t)(key >> 32));
+      } else {
+        left = p.assign[row] == -1;
+      }
+    }
+    if (!__syncthreads_or(left)) continue;
+  }
   // running best of rows wv*16 + 4g + i (identical in the 16 lanes of a group)
   float best[4];
   int bid[4];
@@ -207,11 +227,13 @@ __global__ void __launch_bounds__(256) dresd_kmeans_assign(KmeansParams p) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int64_t row = r0 + wv * 16 + 4 * g + i;
-      if (row < p.n) {
+      if (row < p.n && (!p.only_left || p.assign[row] == -1)) {
         p.assign[row] = bid[i];
         if (p.score) p.score[row] = best[i];
       }
     }
+  }
+  __syncthreads();
   }
 }
 
@@ -292,10 +314,17 @@ hipError_t launch1(F *k, dim3 grid, dim3 block, KmeansParams &p, hipStream_t st)
 
 }  // namespace
 
-hipError_t launch_kmeans_assign(const KmeansParams &pin, hipStream_t st) {
+hipError_t launch_kmeans_assign(const KmeansParams &pin, const AssignParams *left, int cus,
+                                hipStream_t st) {
   if (pin.n == 0) return hipSuccess;
   KmeansParams p = pin;
-  const dim3 grid((unsigned)((p.n + kKR - 1) / kKR));
+  int64_t blocks = (p.n + kKR - 1) / kKR;
+  if (left) {  // mostly a look at the ids: no more workgroups than run at once
+    p.only_left = 1;
+    p.packed = left->packed;
+    blocks = blocks < 2LL * cus ? blocks : 2LL * cus;
+  }
+  const dim3 grid((unsigned)blocks);
   if (p.dtype == kF32) return launch1(dresd_kmeans_assign<kF32>, grid, dim3(256), p, st);
   if (p.dtype == kF16) return launch1(dresd_kmeans_assign<kF16>, grid, dim3(256), p, st);
   return launch1(dresd_kmeans_assign<kBF16>, grid, dim3(256), p, st);

@@ -85,8 +85,36 @@ struct KmeansParams {
   long long *sums;           // [P, d] fixed-point workspace (update)
   int32_t *cnt;              // [P] workspace (update)
   int64_t offset;            // first picked row, in [0, n) (init)
+  int only_left;             // assign only the rows marked -1
+  const uint64_t *packed;    // ... after unpacking (score, id) keys [n], may be null
 };
-hipError_t launch_kmeans_assign(const KmeansParams &p, hipStream_t st);
+// Assignment on the 16-bit matrix cores (dresd_assign.hip).
+struct AssignParams {
+  const void *x;             // [n, d] rows, storage type dtype
+  const float *centroids;    // [P, d]
+  int32_t *assign;           // [n] out; -1: the row is left to the fp32 path
+  float *score;              // [n] out, may be null
+  int64_t n;
+  int d, dtype, P;
+  int KB;                    // blocks of 32 dims, rounded up to a built variant
+  int ppad;                  // P rounded up to whole groups of 64
+  int splits;                // workgroups that share a block of rows
+  // workspace: centroid operands, each centroid's score factor, per centroid
+  // tile whether it needs the fp32 path, and (splits > 1) [n] packed results
+  void *op;
+  float *scale;
+  int32_t *special;
+  uint64_t *packed;
+  int64_t off_scale, off_special, off_packed, bytes;
+};
+constexpr int64_t kAssignMaxOperand = (int64_t)256 << 20;  // bytes of centroid operands
+// Whether rows of this width run there, and the call's shape and workspace.
+bool assign_split_plan(int64_t n, int d, int dtype, int P, int cus, AssignParams *out);
+hipError_t launch_assign_split(AssignParams &p, void *ws, hipStream_t st);
+// The fp32 assignment; with `left` only the rows it marks with id -1 (taking
+// the ids and scores of the others from left->packed first, if set).
+hipError_t launch_kmeans_assign(const KmeansParams &p, const AssignParams *left, int cus,
+                                hipStream_t st);
 hipError_t launch_kmeans_update(const KmeansParams &p, int cus, hipStream_t st);
 hipError_t launch_kmeans_init(const KmeansParams &p, hipStream_t st);
 
