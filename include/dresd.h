@@ -327,8 +327,8 @@ dresd_status dresd_search_plan(const dresd_index *ix, int32_t B, int32_t k,
  *   partition of each key, in [0, P).  Keys are stored grouped by partition
  *   (each partition padded to a 16-row tile); continuations stay in row
  *   order.  Copies everything, synchronises `stream`; the caller may free its
- *   buffers afterwards.  One-time cost: the grouping is a counting sort on
- *   the host.  Errors: EINVAL (nulls, ranges, an assignment outside [0, P)),
+ *   buffers afterwards.  One-time cost: the rows are grouped by a sort on the
+ *   device, with 16 N bytes of temporary memory.  Errors: EINVAL (nulls, ranges, an assignment outside [0, P)),
  *   ENOMEM, EDEVICE.
  * dresd_ivf_search: like dresd_search, probing 1 <= nprobe <= min(P,
  *   DRESD_K_MAX) partitions per query (the nprobe best centroids by inner
@@ -350,9 +350,9 @@ dresd_status dresd_search_plan(const dresd_index *ix, int32_t B, int32_t k,
  *   partition p holds the keys whose continuation starts with the p-th
  *   smallest distinct first token (P = the number of distinct first tokens,
  *   at most DRESD_PARTS_MAX); no centroids.  Arguments as in
- *   dresd_index_create.  Copies everything and reads the first column of
- *   `continuations` back to the host (synchronises `stream`); the grouping is
- *   a host sort of the first tokens.  Errors as dresd_ivf_create.
+ *   dresd_index_create.  Copies everything and synchronises `stream`; the
+ *   grouping is a device sort of the first tokens.  Errors as
+ *   dresd_ivf_create.
  *   dresd_ivf_search and dresd_ivf_search_filtered reject such an index
  *   (EINVAL: no centroids); dresd_ivf_search_probes takes partition ids in
  *   ascending token order.

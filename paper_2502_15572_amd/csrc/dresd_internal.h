@@ -112,16 +112,6 @@ __host__ __device__ inline size_t scan_mq_lds_bytes(int stages, int nqw, int C, 
 constexpr uint32_t kSortedFlag = 0x80000000u;
 
 
-struct LayoutParams {
-  const void *src;           // [N, d] row-major
-  void *dst;                 // tiles
-  const uint32_t *slot_row;  // partitioned layout: row of each slot (null: slot = row)
-  int64_t N;
-  int64_t chunks;            // total 16-byte chunks of the tiled layout
-  int d, KB;
-};
-
-
 // Kernel launch entry points (defined in dresd_kernels.hip).
 typedef void (*ScanKernel)(ScanParams);
 // cpq: columns per query; shared: the variant for launches of several query
@@ -183,7 +173,6 @@ void *merge_kernel_ptr();
 // Bandwidth probe (dresd_bwprobe.hip): one read pass over nblocks 1 KiB
 // blocks with `workgroups` workgroups of 4 waves.
 hipError_t launch_bw_read(const void *buf, int64_t nblocks, int workgroups, hipStream_t st);
-void *layout_kernel_ptr(int dtype);
 int qt_index(int qt);  // 1,2,4,8,16 -> 0..4, else -1
 
 }  // namespace dresd

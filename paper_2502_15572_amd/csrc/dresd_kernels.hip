@@ -2,7 +2,6 @@
 // unit-norm keys and queries, Section 3.4, Eq. 2: the cosine is the inner
 // product; the argmax is taken as the k best keys, Section 3.6).
 //
-//   layout : one-time copy of row-major keys into 16-row MFMA tiles.
 //   scan   : streams the tiles once; MFMA scores (queries as the A operand,
 //            key rows as the B operand); a per-query threshold filter; a
 //            per-wave bounded candidate list, re-selected in LDS when full
@@ -12,38 +11,6 @@
 #include "dresd_scan_common.h"
 
 namespace dresd {
-
-// ---------------------------------------------------------------- layout ---
-
-template <typename T>
-__global__ void __launch_bounds__(256) dresd_layout(LayoutParams p) {
-  constexpr int EPC = 16 / sizeof(T);  // elements per 16-byte chunk
-  const T *src = static_cast<const T *>(p.src);
-  u4 *dst = static_cast<u4 *>(p.dst);
-  for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < p.chunks;
-       c += (int64_t)gridDim.x * blockDim.x) {
-    int64_t per_tile = (int64_t)p.KB * 64;
-    int64_t tile = c / per_tile;
-    int r = (int)(c - tile * per_tile);
-    int kb = r >> 6, ln = r & 63;
-    int64_t row = tile * kTileRows + (ln & 15);
-    if (p.slot_row) {  // partitioned layout: the slot's row, or padding
-      const uint32_t r = p.slot_row[row];
-      row = r == kPadRow ? p.N : (int64_t)r;
-    }
-    int dim0 = kb * 4 * EPC + (ln >> 4) * EPC;
-    union {
-      T e[EPC];
-      u4 v;
-    } u;
-#pragma unroll
-    for (int e = 0; e < EPC; ++e) {
-      int dim = dim0 + e;
-      u.e[e] = (row < p.N && dim < p.d) ? src[row * p.d + dim] : T(0);
-    }
-    dst[c] = u.v;
-  }
-}
 
 // ------------------------------------------------------------------ scan ---
 
@@ -702,11 +669,6 @@ ScanKernel scan_parts_kernel(int dtype) {
   if (dtype == kF16) return (ScanKernel)dresd_scan_parts<kF16, 4>;
   if (dtype == kBF16) return (ScanKernel)dresd_scan_parts<kBF16, 4>;
   return nullptr;
-}
-
-void *layout_kernel_ptr(int dtype) {
-  if (dtype == kF32) return (void *)dresd_layout<float>;
-  return (void *)dresd_layout<uint16_t>;
 }
 #endif
 

@@ -65,12 +65,43 @@ struct SegParams {
   int B, S, P;
 };
 hipError_t launch_segments(const SegParams &p, hipStream_t st);
-// out[i] = cont[i][0], the first token of row i's value.
-hipError_t launch_first_tokens(const int32_t *cont, int L, int64_t n, int32_t *out,
+// Tiled layout of the keys and first-token column (dresd_layout.hip).
+struct LayoutParams {
+  const void *src;           // [N, d] row-major
+  void *dst;                 // tiles
+  const uint32_t *slot_row;  // partitioned layout: row of each slot (null: slot = row)
+  int64_t N, tiles;
+  int d, KB;
+};
+hipError_t launch_layout(const LayoutParams &p, int dtype, int cus, hipStream_t st);
+hipError_t launch_first_tokens(const int32_t *cont, int L, int64_t n, int64_t nslot, int32_t *out,
                                hipStream_t st);
-// ftok[s] = first token of slot s's value (0 for padding slots).
-hipError_t launch_slot_first_tokens(const uint32_t *slot_row, const int32_t *cont, int L,
-                                    int64_t nslot, int32_t *ftok, hipStream_t st);
+// Grouping of rows into partitions (dresd_group.hip).
+constexpr int kGroupTile = 4096;  // rows per workgroup of a sort pass
+struct GroupParams {
+  const int32_t *cont;       // by token: [n, L] values, the key is the first token; else null
+  const int32_t *assign;     // else [n] partition of each row
+  const int32_t *values;     // [n, L] values (first tokens of the slots)
+  int64_t n, nblk, nslot;    // rows, blocks of kGroupTile rows, slots
+  int L, P, by_token;
+  // temporary memory: the keys and rows before and after a pass (`src` holds
+  // the current ones), digit histograms [4][256], positions [256][nblk]
+  uint32_t *key[2], *row[2];
+  uint32_t *hist, *counts;
+  uint32_t *bad, *distinct;  // an assignment outside [0, P); number of distinct keys
+  int src, shift, first;
+  uint32_t *start;           // [P + 1] first sorted position of each partition
+  int32_t *tok;              // by token: [P] the partitions' tokens
+  const int32_t *part_tile;  // [P + 1] first tile of each partition
+  uint32_t *slot_row;        // [nslot] out
+  int32_t *ftok_slot;        // [nslot] out
+};
+hipError_t launch_group_keys(GroupParams &p, hipStream_t st);
+hipError_t launch_group_pass(GroupParams &p, int digit, bool first, hipStream_t st);
+hipError_t launch_group_distinct(GroupParams &p, hipStream_t st);
+hipError_t launch_group_bounds(GroupParams &p, hipStream_t st);
+hipError_t launch_group_slots(GroupParams &p, hipStream_t st);
+hipError_t launch_iota(int32_t *out, int64_t n, hipStream_t st);
 // Spherical k-means (dresd_kmeans.hip).
 struct KmeansParams {
   const void *x;             // [n, d] rows, storage type dtype

@@ -740,21 +740,15 @@ dresd_status index_build(const void *embeddings, const int32_t *continuations, i
   lp.dst = ix->data;
   lp.slot_row = slot_row;
   lp.N = N;
-  lp.chunks = (int64_t)ix->T * ix->KB * 64;
+  lp.tiles = ix->T;
   lp.d = d;
   lp.KB = ix->KB;
-  const int64_t blocks = std::min<int64_t>(ceil_div(lp.chunks, 256), (int64_t)ix->cus * 64);
-  void *args[] = {&lp};
-  hipError_t e = hipLaunchKernel(layout_kernel_ptr(dtype), dim3((unsigned)blocks), dim3(256), args,
-                                 0, st);
+  hipError_t e = launch_layout(lp, dtype, ix->cus, st);
   if (e == hipSuccess)
     e = hipMemcpyAsync(ix->cont, continuations, cont_bytes, hipMemcpyDeviceToDevice, st);
   // First-token column: value[i][0] for every row, zero past N.
   if (e == hipSuccess && ix->ftok)
-    e = hipMemsetAsync(ix->ftok, 0, ftok_bytes, st);
-  if (e == hipSuccess && ix->ftok)
-    e = hipMemcpy2DAsync(ix->ftok, sizeof(int32_t), continuations, (size_t)L * sizeof(int32_t),
-                         sizeof(int32_t), (size_t)N, hipMemcpyDeviceToDevice, st);
+    e = launch_first_tokens(continuations, L, N, ix->T * kTileRows, ix->ftok, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess)
     return cleanup(fail(DRESD_EDEVICE, std::string("index build failed: ") + hipGetErrorString(e)));
@@ -1354,82 +1348,148 @@ static dresd_status check_ivf_args(const void *embeddings, const int32_t *contin
   return DRESD_OK;
 }
 
-// The partitioned index of a host assignment a [N] (ids checked against
-// [0, P)); without centroids it has no centroid index, and its searches
-// take their probes from the caller.
+// The partitioned index of an assignment (centroids and assign set), or of
+// the keys grouped by their value's first token (both null; partition p holds
+// the p-th smallest distinct token; no centroid index, its searches take their
+// probes from the caller or the token).  The rows are grouped on the device
+// (a stable radix sort); the host reads the digits' histogram and the
+// partitions' starts.  The sort's memory is returned before the keys' is
+// taken.
 static dresd_status ivf_build(const void *embeddings, const int32_t *continuations, int64_t N,
                               int32_t d, int32_t L, int32_t dtype, const float *centroids,
-                              int32_t P, std::vector<int32_t> &a, hipStream_t st,
+                              int32_t P, const int32_t *assign, hipStream_t st,
                               dresd_ivf **out) {
-  const dresd_stream stream = st;
-  // Slot table: partitions in id order, each padded to whole tiles, rows of
-  // a partition in row order (a stable counting sort of the assignment).
-  std::vector<int64_t> cnt((size_t)P, 0);
-  for (int64_t i = 0; i < N; ++i) {
-    if (a[i] < 0 || a[i] >= P) return fail(DRESD_EINVAL, "assignment outside [0, P)");
-    ++cnt[a[i]];
+  const bool by_token = assign == nullptr;
+  // What an error (or an exception of the vectors below) leaves behind.
+  struct Building {
+    dresd_ivf *v = nullptr;
+    unsigned char *tmp = nullptr;
+    hipStream_t st;
+    void free_tmp() {
+      if (tmp) (void)hipFree(tmp);
+      tmp = nullptr;
+    }
+    ~Building() {
+      if (tmp) (void)hipStreamSynchronize(st);
+      free_tmp();
+      ivf_free(v);
+    }
+  } hold;
+  hold.st = st;
+  hold.v = new (std::nothrow) dresd_ivf();
+  if (!hold.v) return fail(DRESD_ENOMEM, "host allocation failed");
+  dresd_ivf *v = hold.v;
+  auto device_error = [&](hipError_t e) {
+    return fail(DRESD_EDEVICE, std::string("grouping the keys: ") + hipGetErrorString(e));
+  };
+  // Temporary memory: two (key, row) sequences, histograms, block positions;
+  // the partitions' starts (and tokens) take the sequence that the last pass
+  // read, so the arrays hold P + 1 entries where that is more than N.
+  GroupParams gp = {};
+  gp.n = N;
+  gp.nblk = ceil_div(N, kGroupTile);
+  gp.L = L;
+  gp.P = P;
+  gp.by_token = by_token ? 1 : 0;
+  gp.cont = by_token ? continuations : nullptr;
+  gp.assign = assign;
+  gp.values = continuations;
+  auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+  const size_t seq = up(((size_t)std::max<int64_t>(N, by_token ? 0 : P) + 1) * 4);
+  const size_t off_hist = 4 * seq, off_counts = off_hist + up(1026 * 4);
+  if (dev_alloc((void **)&hold.tmp, off_counts + up((size_t)gp.nblk * 256 * 4)) != hipSuccess) {
+    (void)hipGetLastError();
+    hold.tmp = nullptr;
+    return fail(DRESD_ENOMEM, "memory to group the keys");
   }
+  for (int i = 0; i < 2; ++i) {
+    gp.key[i] = reinterpret_cast<uint32_t *>(hold.tmp + (size_t)(2 * i) * seq);
+    gp.row[i] = reinterpret_cast<uint32_t *>(hold.tmp + (size_t)(2 * i + 1) * seq);
+  }
+  gp.hist = reinterpret_cast<uint32_t *>(hold.tmp + off_hist);
+  gp.bad = gp.hist + 1024;
+  gp.distinct = gp.hist + 1025;
+  gp.counts = reinterpret_cast<uint32_t *>(hold.tmp + off_counts);
+  hipError_t e = launch_group_keys(gp, st);
+  std::vector<uint32_t> hist(1026);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(hist.data(), gp.hist, 1026 * 4, hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  if (e != hipSuccess) return device_error(e);
+  if (!by_token && hist[1024]) return fail(DRESD_EINVAL, "assignment outside [0, P)");
+  // A digit in which all keys agree moves nothing (the first pass also
+  // numbers the rows, so one always runs).
+  bool first = true;
+  for (int dg = 0; dg < 4; ++dg) {
+    bool one = false;
+    for (int i = 0; i < 256; ++i) one |= (int64_t)hist[dg * 256 + i] == N;
+    if (one && !(dg == 3 && first)) continue;
+    e = launch_group_pass(gp, dg, first, st);
+    if (e != hipSuccess) return device_error(e);
+    first = false;
+  }
+  gp.start = gp.key[gp.src ^ 1];
+  gp.tok = reinterpret_cast<int32_t *>(gp.row[gp.src ^ 1]);
+  if (by_token) {
+    e = launch_group_distinct(gp, st);
+    uint32_t count = 0;
+    if (e == hipSuccess) e = hipMemcpyAsync(&count, gp.distinct, 4, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return device_error(e);
+    if ((int64_t)count > DRESD_PARTS_MAX)
+      return fail(DRESD_EINVAL, "more distinct first tokens than DRESD_PARTS_MAX");
+    P = gp.P = (int32_t)count;
+  } else {
+    e = launch_group_bounds(gp, st);
+    if (e != hipSuccess) return device_error(e);
+  }
+  std::vector<uint32_t> start((size_t)P + 1);
+  e = hipMemcpyAsync(start.data(), gp.start, start.size() * 4, hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  if (e != hipSuccess) return device_error(e);
+  // Partitions in id order, each padded to whole tiles.
   std::vector<int32_t> pt((size_t)P + 1);
   int64_t T = 0;
+  double sq = 0.0;  // sum over partitions of their tile counts squared
   for (int32_t p = 0; p < P; ++p) {
     pt[p] = (int32_t)T;
-    T += ceil_div(cnt[p], kTileRows);
+    const int64_t tiles = ceil_div((int64_t)start[p + 1] - (int64_t)start[p], kTileRows);
+    T += tiles;
+    sq += (double)tiles * (double)tiles;
   }
   pt[P] = (int32_t)T;
-  double sq = 0.0;  // sum over partitions of their tile counts squared
-  for (int32_t p = 0; p < P; ++p) sq += (double)(pt[p + 1] - pt[p]) * (double)(pt[p + 1] - pt[p]);
-  std::vector<uint32_t> slot((size_t)T * kTileRows, kPadRow);
-  std::vector<int64_t> next((size_t)P);
-  for (int32_t p = 0; p < P; ++p) next[p] = (int64_t)pt[p] * kTileRows;
-  for (int64_t i = 0; i < N; ++i) slot[next[a[i]]++] = (uint32_t)i;
-  a.clear();
-  a.shrink_to_fit();
-
-  dresd_ivf *v = new (std::nothrow) dresd_ivf();
-  if (!v) return fail(DRESD_ENOMEM, "host allocation failed");
   v->P = P;
   v->probe_tiles = std::max<int64_t>(1, (int64_t)(sq / (double)std::max<int64_t>(1, T)));
-  auto bail = [&](dresd_status s) {
-    ivf_free(v);
-    return s;
-  };
-  if (dev_alloc((void **)&v->slot_row, slot.size() * 4) != hipSuccess ||
-      dev_alloc((void **)&v->ftok_slot, slot.size() * 4) != hipSuccess ||
-      dev_alloc((void **)&v->part_tile, pt.size() * 4) != hipSuccess) {
+  gp.nslot = T * kTileRows;
+  if (dev_alloc((void **)&v->slot_row, (size_t)gp.nslot * 4) != hipSuccess ||
+      dev_alloc((void **)&v->ftok_slot, (size_t)gp.nslot * 4) != hipSuccess ||
+      dev_alloc((void **)&v->part_tile, pt.size() * 4) != hipSuccess ||
+      (by_token && dev_alloc((void **)&v->tok, (size_t)P * 4) != hipSuccess)) {
     (void)hipGetLastError();
-    return bail(fail(DRESD_ENOMEM, "slot table allocation failed"));
+    return fail(DRESD_ENOMEM, "slot table allocation failed");
   }
-  if (hipMemcpy(v->slot_row, slot.data(), slot.size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(v->part_tile, pt.data(), pt.size() * 4, hipMemcpyHostToDevice) != hipSuccess)
-    return bail(fail(DRESD_EDEVICE, "slot table upload failed"));
-  // First token of each slot's value (the next-token filter).
-  if (launch_slot_first_tokens(v->slot_row, continuations, L, (int64_t)slot.size(), v->ftok_slot,
-                               st) != hipSuccess ||
-      hipStreamSynchronize(st) != hipSuccess)
-    return bail(fail(DRESD_EDEVICE, "first-token column build failed"));
-  dresd_status s = index_build(embeddings, continuations, N, d, L, dtype, v->slot_row, T, stream,
-                               &v->ix);
-  if (s != DRESD_OK) return bail(s);
-  if (!centroids) {
-    *out = v;
-    return DRESD_OK;
+  gp.part_tile = v->part_tile;
+  gp.slot_row = v->slot_row;
+  gp.ftok_slot = v->ftok_slot;
+  e = hipMemcpyAsync(v->part_tile, pt.data(), pt.size() * 4, hipMemcpyHostToDevice, st);
+  if (e == hipSuccess) e = launch_group_slots(gp, st);
+  if (e == hipSuccess && by_token)
+    e = hipMemcpyAsync(v->tok, gp.tok, (size_t)P * 4, hipMemcpyDeviceToDevice, st);
+  if (e == hipSuccess && !by_token)  // values of the centroid index: the partition ids
+    e = launch_iota(reinterpret_cast<int32_t *>(gp.key[gp.src]), P, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  if (e != hipSuccess) return device_error(e);
+  dresd_status s = DRESD_OK;
+  if (!by_token) {
+    s = index_build(centroids, reinterpret_cast<int32_t *>(gp.key[gp.src]), P, d, 1, DRESD_F32,
+                    nullptr, 0, st, &v->cix);
+    if (s != DRESD_OK) return s;
   }
-  // Centroid index: fp32 keys, value = the partition id.
-  std::vector<int32_t> ids((size_t)P);
-  for (int32_t p = 0; p < P; ++p) ids[p] = p;
-  int32_t *ids_dev = nullptr;
-  if (dev_alloc((void **)&ids_dev, (size_t)P * 4) != hipSuccess) {
-    (void)hipGetLastError();
-    return bail(fail(DRESD_ENOMEM, "allocation failed"));
-  }
-  if (hipMemcpy(ids_dev, ids.data(), (size_t)P * 4, hipMemcpyHostToDevice) != hipSuccess) {
-    (void)hipFree(ids_dev);
-    return bail(fail(DRESD_EDEVICE, "partition id upload failed"));
-  }
-  s = index_build(centroids, ids_dev, P, d, 1, DRESD_F32, nullptr, 0, stream, &v->cix);
-  (void)hipFree(ids_dev);
-  if (s != DRESD_OK) return bail(s);
+  hold.free_tmp();
+  s = index_build(embeddings, continuations, N, d, L, dtype, v->slot_row, T, st, &v->ix);
+  if (s != DRESD_OK) return s;
   *out = v;
+  hold.v = nullptr;
   return DRESD_OK;
 }
 
@@ -1441,11 +1501,8 @@ static dresd_status ivf_create_impl(const void *embeddings, const int32_t *conti
   dresd_status s = check_ivf_args(embeddings, continuations, N, d, L, dtype);
   if (s != DRESD_OK) return s;
   if (P < 1 || P > DRESD_PARTS_MAX) return fail(DRESD_EINVAL, "P out of range");
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  std::vector<int32_t> a((size_t)N);
-  DRESD_HIP(hipMemcpyAsync(a.data(), assign, (size_t)N * 4, hipMemcpyDeviceToHost, st));
-  DRESD_HIP(hipStreamSynchronize(st));
-  return ivf_build(embeddings, continuations, N, d, L, dtype, centroids, P, a, st, out);
+  return ivf_build(embeddings, continuations, N, d, L, dtype, centroids, P, assign,
+                   static_cast<hipStream_t>(stream), out);
 }
 
 // Keys grouped by the first token of their value: partition p holds the
@@ -1456,49 +1513,15 @@ static dresd_status ivf_by_token_impl(const void *embeddings, const int32_t *con
   if (!out) return fail(DRESD_EINVAL, "NULL pointer argument");
   dresd_status s = check_ivf_args(embeddings, continuations, N, d, L, dtype);
   if (s != DRESD_OK) return s;
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  std::vector<int32_t> a((size_t)N);  // first tokens, then their partitions
-  {
-    // gathered on the device, then one contiguous copy
-    int32_t *col = nullptr;
-    if (dev_alloc((void **)&col, (size_t)N * 4) != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(DRESD_ENOMEM, "first-token column allocation failed");
-    }
-    hipError_t e = launch_first_tokens(continuations, L, N, col, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(a.data(), col, (size_t)N * 4, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    (void)hipFree(col);
-    if (e != hipSuccess) return fail(DRESD_EDEVICE, std::string("first-token column: ") + hipGetErrorString(e));
-  }
-  std::vector<int32_t> tok(a);
-  std::sort(tok.begin(), tok.end());
-  tok.erase(std::unique(tok.begin(), tok.end()), tok.end());
-  if ((int64_t)tok.size() > DRESD_PARTS_MAX)
-    return fail(DRESD_EINVAL, "more distinct first tokens than DRESD_PARTS_MAX");
-  const int32_t P = (int32_t)tok.size();
-  for (int32_t &x : a) x = (int32_t)(std::lower_bound(tok.begin(), tok.end(), x) - tok.begin());
-  dresd_ivf *v = nullptr;
-  s = ivf_build(embeddings, continuations, N, d, L, dtype, nullptr, P, a, st, &v);
-  if (s != DRESD_OK) return s;
-  if (dev_alloc((void **)&v->tok, (size_t)P * 4) != hipSuccess) {
-    (void)hipGetLastError();
-    ivf_free(v);
-    return fail(DRESD_ENOMEM, "token table allocation failed");
-  }
-  if (hipMemcpy(v->tok, tok.data(), (size_t)P * 4, hipMemcpyHostToDevice) != hipSuccess) {
-    ivf_free(v);
-    return fail(DRESD_EDEVICE, "token table upload failed");
-  }
-  *out = v;
-  return DRESD_OK;
+  return ivf_build(embeddings, continuations, N, d, L, dtype, nullptr, 0, nullptr,
+                   static_cast<hipStream_t>(stream), out);
 }
 
 dresd_status dresd_ivf_create(const void *embeddings, const int32_t *continuations, int64_t N,
                               int32_t d, int32_t L, int32_t dtype, const float *centroids,
                               int32_t P, const int32_t *assign, dresd_stream stream,
                               dresd_ivf **out) {
-  // the slot table is built on the host: its vectors may fail to allocate
+  // the partitions' starts go through the host: their vectors may fail to allocate
   try {
     return ivf_create_impl(embeddings, continuations, N, d, L, dtype, centroids, P, assign, stream,
                            out);
