@@ -66,6 +66,131 @@ dresd_status fail(dresd_status s, const std::string &msg) {
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// Large blocks that destroyed indexes and finished builds gave up, kept for
+// the next build.  The driver wipes released memory at about 35 GB/s and makes
+// hipFree wait for it: rebuilding a 1.3 GB index in a loop spent 31 of 38 ms
+// there.  Bounded: blocks of at least 64 MiB, together at most 1/128 of the
+// device's memory (2.25 GiB of 288), the oldest released first; all of them
+// are released as soon as an allocation fails.  A block is kept only after the
+// device has finished with it (as hipFree would wait), so it may be used again
+// on any stream and from any thread.
+struct BlockCache {
+  static constexpr size_t kMinBlock = (size_t)64 << 20;
+  struct Block {
+    void *ptr;
+    size_t bytes;
+    int dev;
+  };
+  std::mutex mu;
+  std::map<void *, std::pair<size_t, int>> live;  // large blocks handed out: size, device
+  std::vector<Block> kept;                        // oldest first
+
+  // Sizes in steps of 1/32 of their power of two, so that builds of nearly
+  // the same size can use one another's blocks.
+  static size_t rounded(size_t bytes) {
+    size_t g = kMinBlock;
+    while (2 * g <= bytes) g *= 2;
+    g /= 32;
+    return (bytes + g - 1) / g * g;
+  }
+  void release(int dev) {
+    size_t n = 0;
+    for (const Block &b : kept) {
+      if (b.dev == dev) (void)hipFree(b.ptr);
+      else kept[n++] = b;
+    }
+    kept.resize(n);
+  }
+  hipError_t take(void **ptr, size_t bytes) {
+    *ptr = nullptr;
+    try {
+      return take_block(ptr, bytes);
+    } catch (const std::bad_alloc &) {  // the host's own lists
+      if (*ptr) (void)hipFree(*ptr);
+      *ptr = nullptr;
+      return hipErrorOutOfMemory;
+    }
+  }
+  hipError_t take_block(void **ptr, size_t bytes) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lock(mu);
+    size_t unused = 0, total = 0, held = 0;
+    if (bytes >= kMinBlock) {
+      e = hipMemGetInfo(&unused, &total);
+      if (e != hipSuccess) return e;
+    }
+    const size_t want = rounded(bytes);
+    if (bytes >= kMinBlock && want <= total / 128) {  // a size that may be kept
+      kept.reserve(kept.size() + live.size() + 2);    // give() allocates nothing
+      for (size_t i = 0; i < kept.size(); ++i)
+        if (kept[i].dev == dev && kept[i].bytes == want) {
+          live[kept[i].ptr] = {want, dev};
+          *ptr = kept[i].ptr;
+          kept.erase(kept.begin() + (ptrdiff_t)i);
+          return hipSuccess;
+        }
+      e = hipMalloc(ptr, want);
+      if (e == hipSuccess) {
+        live[*ptr] = {want, dev};
+        return e;
+      }
+    } else {
+      e = hipMalloc(ptr, bytes);
+      if (e == hipSuccess) return e;
+    }
+    // Out of memory: what is kept goes back, if that makes the room.
+    (void)hipGetLastError();
+    *ptr = nullptr;
+    for (const Block &b : kept)
+      if (b.dev == dev) held += b.bytes;
+    if (hipMemGetInfo(&unused, &total) != hipSuccess || unused + held < bytes) return e;
+    release(dev);
+    return hipMalloc(ptr, bytes);
+  }
+  void give(void *ptr) {
+    if (!ptr) return;
+    std::lock_guard<std::mutex> lock(mu);
+    const auto it = live.find(ptr);
+    size_t total = 0, most = 0, unused = 0;
+    int cur = -1;
+    if (it != live.end()) {
+      const Block b = {ptr, it->second.first, it->second.second};
+      live.erase(it);
+      if (hipGetDevice(&cur) == hipSuccess && cur == b.dev &&
+          hipMemGetInfo(&unused, &most) == hipSuccess && b.bytes <= most / 128 &&
+          hipDeviceSynchronize() == hipSuccess) {
+        most /= 128;
+        total = b.bytes;
+        for (const Block &k : kept)
+          if (k.dev == cur) total += k.bytes;
+        for (size_t i = 0; i < kept.size() && total > most;) {
+          if (kept[i].dev == cur) {
+            total -= kept[i].bytes;
+            (void)hipFree(kept[i].ptr);
+            kept.erase(kept.begin() + (ptrdiff_t)i);
+          } else {
+            ++i;
+          }
+        }
+        kept.push_back(b);
+        return;
+      }
+      (void)hipGetLastError();
+    }
+    (void)hipFree(ptr);
+  }
+};
+
+BlockCache &block_cache() {
+  static BlockCache *c = new BlockCache();  // outlives every index, static ones too
+  return *c;
+}
+
+// Releases what dev_alloc returned (waiting for the device like hipFree).
+void dev_free(void *ptr) { block_cache().give(ptr); }
+
 // Every device allocation of the library goes through here.  Test hook: with
 // DRESD_FAIL_ALLOC_AT=n in the environment, the n-th allocation counted since
 // the variable last changed fails as out of memory without allocating, so
@@ -91,7 +216,7 @@ hipError_t dev_alloc(void **ptr, size_t bytes) {
       }
     }
   }
-  return hipMalloc(ptr, bytes);
+  return block_cache().take(ptr, bytes);
 }
 
 // A buffer may only grow outside stream capture: growing allocates and
@@ -520,7 +645,7 @@ dresd_status ensure_workspace(dresd_index *ix, size_t bytes, hipStream_t st,
   // ordered on the search's own stream (not capturing: growth is refused
   // then), ahead of the kernels that use the workspace.
   if (hipMemsetAsync(p, 0, bytes, st) != hipSuccess) {
-    (void)hipFree(p);
+    dev_free(p);
     return fail(DRESD_EDEVICE, "workspace clear failed");
   }
   // The outgrown buffer is kept until the index is destroyed: a graph
@@ -651,9 +776,9 @@ dresd_status index_build(const void *embeddings, const int32_t *continuations, i
   dresd_index *ix = new (std::nothrow) dresd_index();
   if (!ix) return fail(DRESD_ENOMEM, "host allocation failed");
   auto cleanup = [&](dresd_status s) {
-    if (ix->data) (void)hipFree(ix->data);
-    if (ix->cont) (void)hipFree(ix->cont);
-    if (ix->ftok) (void)hipFree(ix->ftok);
+    if (ix->data) dev_free(ix->data);
+    if (ix->cont) dev_free(ix->cont);
+    if (ix->ftok) dev_free(ix->ftok);
     delete ix;
     return s;
   };
@@ -775,12 +900,12 @@ void dresd_index_destroy(dresd_index *ix) {
   (void)hipGetDevice(&cur);
   (void)hipSetDevice(ix->device);
   (void)hipDeviceSynchronize();
-  if (ix->data) (void)hipFree(ix->data);
-  if (ix->cont) (void)hipFree(ix->cont);
-  if (ix->ftok) (void)hipFree(ix->ftok);
+  if (ix->data) dev_free(ix->data);
+  if (ix->cont) dev_free(ix->cont);
+  if (ix->ftok) dev_free(ix->ftok);
   for (auto &w : ix->ws)
-    if (w.second.first) (void)hipFree(w.second.first);
-  for (void *r : ix->retired) (void)hipFree(r);
+    if (w.second.first) dev_free(w.second.first);
+  for (void *r : ix->retired) dev_free(r);
   for (auto e : ix->ev_free) (void)hipEventDestroy(e);
   for (auto e : profile_events(ix)) (void)hipEventDestroy(e);
   (void)hipSetDevice(cur);
@@ -1187,13 +1312,13 @@ void ivf_free(dresd_ivf *v) {
   if (!v) return;
   if (v->ix) dresd_index_destroy(v->ix);
   if (v->cix) dresd_index_destroy(v->cix);
-  if (v->slot_row) (void)hipFree(v->slot_row);
-  if (v->ftok_slot) (void)hipFree(v->ftok_slot);
-  if (v->part_tile) (void)hipFree(v->part_tile);
-  if (v->tok) (void)hipFree(v->tok);
+  if (v->slot_row) dev_free(v->slot_row);
+  if (v->ftok_slot) dev_free(v->ftok_slot);
+  if (v->part_tile) dev_free(v->part_tile);
+  if (v->tok) dev_free(v->tok);
   for (auto &pb : v->probe)
-    if (pb.second.first) (void)hipFree(pb.second.first);
-  for (void *r : v->retired) (void)hipFree(r);
+    if (pb.second.first) dev_free(pb.second.first);
+  for (void *r : v->retired) dev_free(r);
   delete v;
 }
 
@@ -1366,7 +1491,7 @@ static dresd_status ivf_build(const void *embeddings, const int32_t *continuatio
     unsigned char *tmp = nullptr;
     hipStream_t st;
     void free_tmp() {
-      if (tmp) (void)hipFree(tmp);
+      if (tmp) dev_free(tmp);
       tmp = nullptr;
     }
     ~Building() {
@@ -1592,7 +1717,7 @@ dresd_status ivf_search_impl(dresd_ivf *v, const float *queries, const int32_t *
       return fail(DRESD_ENOMEM, "probe buffer allocation failed");
     }
     if (hipMemsetAsync(p, 0, (size_t)need, st) != hipSuccess) {  // ordered on the search's stream
-      (void)hipFree(p);
+      dev_free(p);
       return fail(DRESD_EDEVICE, "probe buffer clear failed");
     }
     // kept until destroy: a captured graph may still use the outgrown buffer

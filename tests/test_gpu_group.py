@@ -108,3 +108,53 @@ def test_group_by_partition(gpu_lib, n, P):
         a[n - 1] = bad
         with pytest.raises(DresdError, match="outside"):
             PartitionedIndex(keys.to(DEV), dev[0], dev[1], torch.from_numpy(a).to(DEV))
+
+
+def test_released_blocks_are_bounded(gpu_lib):
+    """Large blocks of destroyed indexes are kept for the next build, never
+    more than 1/128 of the device's memory, and builds on them give the same
+    answers (also from two threads at once)."""
+    import threading
+    from paper_2502_15572_amd import Index, PartitionedIndex
+    say("released blocks")
+    d, L = 64, 2
+    torch.cuda.synchronize()
+    total = torch.cuda.mem_get_info()[1]
+    q = torch.randn(2, d, device=DEV)
+    data = []
+    for n in (700000, 701000, 1500000):  # 90 MB keys and up
+        keys = torch.randn(n, d, device=DEV).to(torch.float16)
+        cont = torch.randint(0, 50, (n, L), device=DEV, dtype=torch.int32)
+        ix = Index(keys, cont)
+        data.append((keys, cont, ix.search(q, 5)))
+        ix.close()
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    bad = []
+
+    def build(order):
+        s = torch.cuda.Stream()
+        for i in order:
+            keys, cont, ref = data[i]
+            with torch.cuda.stream(s):
+                ix = Index(keys, cont, stream=s)
+                tix = PartitionedIndex.by_first_token(keys, cont, stream=s)
+                got = ix.search(q, 5, stream=s)
+                nt = got[2][:, 0, 0].contiguous()
+                best = tix.search_next_token(q, nt, 1, stream=s)
+                s.synchronize()
+            if not all(torch.equal(a, b) for a, b in zip(got, ref)) or \
+                    not torch.equal(best[0][:, 0], ref[0][:, 0]):
+                bad.append(i)
+            ix.close()
+            tix.close()
+
+    threads = [threading.Thread(target=build, args=(o,)) for o in ((0, 1, 2, 0), (2, 1, 0, 1))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
+    torch.cuda.synchronize()
+    # (torch may have taken a few MB of its own meanwhile)
+    assert free0 - torch.cuda.mem_get_info()[0] <= total // 128 + (64 << 20)
