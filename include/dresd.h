@@ -254,7 +254,10 @@ dresd_status dresd_bw_probe(const void *buf, int64_t bytes, int32_t reps, int32_
  *   eps_n   finite, >= 0 (the eps of Eq. 2; 1e-12 is a common choice).
  *   y       device, [M, l] fp32 row-major output (ready for dresd_search).
  *   stream  stream the transform runs on (asynchronous).
- * Arithmetic: fp32, the projection on the fp32 matrix cores; batches with
+ * Arithmetic: fp32, the projection on the fp32 matrix cores, or for large
+ * batches (at least 512 rows and about 2^30 multiply-adds) on the 16-bit ones
+ * with z and W in three bf16 parts each that sum to them (error no larger; a
+ * workspace of 6 D l bytes, at most 256 MiB; without it in fp32); batches with
  * few output tiles split D across workgroups and add the partial sums in a
  * fixed order, so results are deterministic.  Ownership: all buffers are
  * caller-owned and must stay alive until `stream` completes; the partial sums

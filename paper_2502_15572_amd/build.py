@@ -36,7 +36,8 @@ UNITS = [("dresd_kernels.hip", ["-DDRESD_TU=%d" % t], "kernels%d" % t) for t in 
     ("dresd_merge.hip", [], "merge"), ("dresd_transform.hip", [], "transform"),
     ("dresd_drafts.hip", [], "drafts"), ("dresd_parts.hip", [], "parts"),
     ("dresd_kmeans.hip", [], "kmeans"), ("dresd_assign.hip", [], "assign"),
-    ("dresd_group.hip", [], "group"), ("dresd_layout.hip", [], "layout"), ("dresd_bwprobe.hip", [], "bwprobe"),
+    ("dresd_group.hip", [], "group"), ("dresd_layout.hip", [], "layout"),
+    ("dresd_project.hip", [], "project"), ("dresd_bwprobe.hip", [], "bwprobe"),
     ("dresd_runtime.hip", [], "runtime")]
 
 

@@ -44,6 +44,18 @@ struct TransformParams {
 int transform_splits(int64_t M, int D, int l, int cus);
 hipError_t launch_transform(const TransformParams &p, hipStream_t st);
 
+// Datastore-sized batches on the 16-bit matrix cores (dresd_project.hip).
+struct ProjectParams {
+  TransformParams t;         // splits: slices of whole 32-dim blocks (dslice unused)
+  void *op;                  // weight operands
+  float *norm;               // [KB][64] means and factors of a block's dims
+  int KB, NT, groups;        // 32-dim blocks, column tiles per workgroup, column groups
+  int64_t off_norm, off_part, bytes;  // workspace
+};
+// Whether a batch runs there, and its shape and workspace.
+bool project_split_plan(int64_t M, int D, int l, int cus, ProjectParams *out);
+hipError_t launch_project_split(ProjectParams &p, void *ws, hipStream_t st);
+
 // Draft assembly (dresd_drafts.hip): tokens [B, k, L] -> drafts [B, r, length],
 // count [B].
 struct DraftParams {

@@ -1202,6 +1202,28 @@ dresd_status dresd_transform(const float *x, int64_t M, int32_t D, const float *
   DRESD_HIP(hipGetDevice(&dev));
   int cus = 0;
   DRESD_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  static DeviceBuffers bufs;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  // Large batches on the 16-bit matrix cores; without a workspace for their
+  // weight operands (memory, or a first call inside a capture) in fp32.
+  ProjectParams pp;
+  if (project_split_plan(M, D, l, cus, &pp)) {
+    void *b = nullptr;
+    if (device_buffer(bufs, dev, (size_t)pp.bytes, st, "transform workspace", &b) == DRESD_OK) {
+      pp.t.x = x;
+      pp.t.mean = mean;
+      pp.t.var = var;
+      pp.t.W = W;
+      pp.t.y = y;
+      pp.t.M = M;
+      pp.t.D = D;
+      pp.t.l = l;
+      pp.t.eps_z = eps_z;
+      pp.t.eps_n = eps_n;
+      DRESD_HIP(launch_project_split(pp, b, st));
+      return DRESD_OK;
+    }
+  }
   TransformParams p;
   p.splits = transform_splits(M, D, l, cus);
   p.dslice = (int)ceil_div(D, p.splits);
@@ -1209,11 +1231,9 @@ dresd_status dresd_transform(const float *x, int64_t M, int32_t D, const float *
   if (p.splits > 1) {
     // Partial sums of the D slices (a per-device buffer kept for the life of
     // the process).
-    static DeviceBuffers bufs;
     const size_t need = (size_t)p.splits * (size_t)M * (size_t)l * sizeof(float);
     void *b = nullptr;
-    dresd_status s = device_buffer(bufs, dev, need, static_cast<hipStream_t>(stream),
-                                   "transform workspace", &b);
+    dresd_status s = device_buffer(bufs, dev, need, st, "transform workspace", &b);
     if (s != DRESD_OK) return s;
     p.part = static_cast<float *>(b);
   }
@@ -1227,7 +1247,7 @@ dresd_status dresd_transform(const float *x, int64_t M, int32_t D, const float *
   p.l = l;
   p.eps_z = eps_z;
   p.eps_n = eps_n;
-  DRESD_HIP(launch_transform(p, static_cast<hipStream_t>(stream)));
+  DRESD_HIP(launch_transform(p, st));
   return DRESD_OK;
 }
 

@@ -1,0 +1,102 @@
+"""The transform of datastore-sized batches on the 16-bit matrix cores (from
+about 2^30 multiply-adds on) at the edges of its variants: each number of
+column tiles, several column groups, ragged rows, dims (with 16- and 4-byte
+copies) and columns, D split or not, whole rows normalised in the kernel or
+after it.  Bound: the fp32 bound of test_gpu_transform, per element; rows that
+the split into bf16 parts does not hold come out as the fp32 kernels give them
+(rows computed by themselves, below the path's size)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from test_gpu_transform import DEV, bound, make_case, run
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # M, D, l
+    (66000, 1024, 16),     # one column tile; whole rows
+    (40001, 512, 32),      # two
+    (16385, 1030, 33),     # three; rows of x 8 bytes off 16
+    (9000, 999, 64),       # four; 4-byte copies
+    (7001, 1001, 80),      # five, the last dims past D
+    (1025, 4096, 128),     # D split, one row past four blocks
+    (2049, 2500, 107),     # seven tiles, a column short
+    (66049, 128, 127),     # four blocks of dims, whole rows, one row in the last block
+    (70001, 64, 130),      # two column groups of five tiles, not split
+    (513, 2048, 1025),     # nine groups
+    (600, 3333, 300),
+]
+
+
+@pytest.mark.parametrize("M,D,l", SHAPES, ids=["M%d-D%d-l%d" % s for s in SHAPES])
+def test_project_split(gpu_lib, M, D, l):
+    print("project split", M, D, l, flush=True)
+    assert M * D * l >= 2 ** 29
+    x, mean, var, W = make_case(M, D, l, seed=M + D + l)
+    x[M // 2] = mean
+    got = run(x, mean, var, W)
+    step = max(1, 40000000 // D)
+    for r in range(0, M, step):
+        want = oracle.transform(x[r:r + step], mean, var, W, 1e-5, 1e-12)
+        err = np.abs(got[r:r + step] - want)
+        tol = bound(x[r:r + step], mean, var, W, 1e-5, want)
+        assert np.all(err <= tol), (float(err.max()), float((err / tol).max()))
+    assert not got[M // 2].any()
+
+
+@pytest.mark.parametrize("M,D,l", [(66000, 128, 128), (1030, 4096, 256)])
+def test_rows_computed_again(gpu_lib, M, D, l):
+    """Infinities, NaN, values past bf16's rounding range and rows of
+    vanishing size: as computed by themselves (fp32 kernels)."""
+    from paper_2502_15572_amd import transform
+    print("rows computed again", M, D, l, flush=True)
+    x, mean, var, W = make_case(M, D, l, seed=3)
+    mean[:] = 0.0
+    var[:] = 1.0
+    W[7] = 0.0               # an infinity there meets zero weights
+    odd = {0: (7, np.inf), 31: (5, np.inf), 33: (D - 1, -np.inf), 300: (2, np.nan),
+           M - 2: (9, 3.4e38)}
+    clean = x.copy()
+    for r, (j, v) in odd.items():
+        x[r, j] = v
+    x[300 + 1, 3], x[300 + 1, 4] = np.inf, -np.inf
+    x[M - 1] = clean[M - 1] * np.float32(1e-25)
+    rows = sorted(list(odd) + [301, M - 1])
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+    args = (t(mean), t(var), t(W))
+    got = transform(t(x), *args, eps_z=0.0, eps_n=0.0)
+    ref = transform(t(clean), *args, eps_z=0.0, eps_n=0.0)
+    alone = transform(t(x[rows]), *args, eps_z=0.0, eps_n=0.0)
+    torch.cuda.synchronize()
+    g, a = got[rows].cpu().numpy(), alone.cpu().numpy()
+    assert np.array_equal(np.isnan(g), np.isnan(a))
+    assert np.array_equal(np.isinf(g), np.isinf(a))
+    fin = np.isfinite(a)
+    assert np.array_equal(g[~fin & ~np.isnan(a)], a[~fin & ~np.isnan(a)])
+    assert np.all(np.abs(g[fin] - a[fin]) <= (D + 10) * 2.0 ** -22)
+    rest = torch.ones(M, dtype=torch.bool)
+    rest[rows] = False
+    rest = rest.to(DEV)
+    assert torch.equal(got[rest], ref[rest])
+
+
+def test_project_first_call_inside_capture(gpu_lib):
+    """No workspace yet on a capturing stream: the fp32 kernels run."""
+    from paper_2502_15572_amd import transform
+    M, D, l = 70000, 128, 128   # D not split: those kernels need no workspace
+    x, mean, var, W = make_case(M, D, l, seed=5)
+    t = lambda a: torch.from_numpy(a).to(DEV)
+    args = (t(x), t(mean), t(var), t(W))
+    want = transform(*args)
+    s = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        y = transform(*args, stream=s)
+    for _ in range(3):
+        y.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.allclose(y, want, rtol=0, atol=(D + 10) * 2.0 ** -22)
