@@ -7,8 +7,12 @@
 //
 // Latency matters more than throughput here (one short kernel per pass), so
 // every step is one round of independent loads followed by a few barriers:
-// list summaries, then all listed keys at once (flattened over lists), and
-// radix selections that start at the highest bit where the keys differ.
+// list summaries, then all listed keys at once (8 lanes per 8 keys of a kept
+// list, so no thread searches for its key), and radix selections that start
+// at the highest bit where the keys differ.  The bound over the lists' best
+// keys stops after two digits: it then keeps a few lists more than the exact
+// k-th best would, which cost less than another digit's barriers.
+// Measured: @MERGE@
 #include "dresd_device.h"
 #include "dresd_ops.h"
 
@@ -19,16 +23,17 @@ constexpr int kSmallMerge = 256;
 // Winner counts up to this are ordered by rank, larger ones by a bitonic
 // network over the workgroup.
 constexpr int kRankSortMax = 512;
-// Each thread owns this many lists (their offsets share the histogram).
+// Each thread looks at this many lists.
 constexpr int kListsPerThread = kMergeLists / kMergeThreads;
+// Work items of the gather (64 keys of a kept list each) held in LDS.
+constexpr uint32_t kMergeItems = kMergeLists;
 
 struct MergeShared {
-  uint32_t hist[kMergeLists];  // radix histogram (256 bins); list offsets during the gather
-  uint32_t part[kMergeThreads / kWaveSize];
+  uint32_t hist[kMergeItems];  // radix histogram (256 bins); the gather's work items
   alignas(16) uint64_t cache[kMergeCap];
   alignas(16) uint64_t win[DRESD_K_MAX_INTERNAL];
   uint64_t sel_prefix, sel_mask, bound, v_and, v_or;
-  uint32_t sel_krem, sel_done, win_cnt, ncand, total, any_known;
+  uint32_t sel_krem, sel_done, win_cnt, ncand, total8, total64, any_known;
 };
 
 __device__ inline uint64_t wave_and(uint64_t v) {
@@ -83,9 +88,11 @@ __device__ inline void rank_sort_desc(const uint64_t *src, uint32_t n, uint64_t 
 // time from the highest bit in which the values differ: every thread adds
 // its values to the 256-bin histogram, then one wave finds the bin holding
 // the kk-th largest (and clears the histogram), two barriers per digit.
-// Called by the whole workgroup.
+// Called by the whole workgroup.  After at most `digits` digits it returns
+// the lower boundary of the bin reached: at least kk values lie at or above it.
 template <class Src>
-__device__ uint64_t radix_kth(MergeShared &sh, Src src, uint32_t M, uint32_t kk) {
+__device__ uint64_t radix_kth(MergeShared &sh, Src src, uint32_t M, uint32_t kk,
+                              int digits = 8) {
   constexpr int kDigit = 8, kBins = 1 << kDigit, kBinsPerLane = kBins / kWaveSize;
   const int tid = threadIdx.x, nth = blockDim.x;
   const int lane = tid & (kWaveSize - 1), wid = tid / kWaveSize;
@@ -162,7 +169,7 @@ __device__ uint64_t radix_kth(MergeShared &sh, Src src, uint32_t M, uint32_t kk)
     pm = sh.sel_mask;
     krem = sh.sel_krem;
     top = s - 1;
-    if (sh.sel_done || top < 0) break;
+    if (sh.sel_done || top < 0 || --digits == 0) break;
     // wave 0 rewrites the state only after the next histogram's barrier,
     // which every thread reaches after reading it
   }
@@ -255,16 +262,18 @@ __global__ void __launch_bounds__(kMergeThreads) dresd_merge(MergeParams p) {
     sh.ncand = 0;
     sh.win_cnt = 0;
     sh.any_known = 0;
+    sh.total8 = 0;
+    sh.total64 = 0;
   }
   __syncthreads();
-  // Thread t owns lists [L t, L t + L), L = kListsPerThread.
+  // Thread t looks at lists t, t + 1024, ...
   uint32_t cnt[kListsPerThread];
   uint64_t first[kListsPerThread];
   uint64_t mb = 0;
   bool known = false;
 #pragma unroll
   for (int j = 0; j < kListsPerThread; ++j) {
-    const int w = tid * kListsPerThread + j;
+    const int w = tid + j * kMergeThreads;
     cnt[j] = 0;
     first[j] = 0;
     if (w < G) {
@@ -272,6 +281,12 @@ __global__ void __launch_bounds__(kMergeThreads) dresd_merge(MergeParams p) {
       first[j] = lfirst[w];
       const uint64_t v = lkth[w];
       mb = v > mb ? v : mb;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kListsPerThread; ++j) {
+    const int w = tid + j * kMergeThreads;
+    if (w < G) {
       const uint64_t f = first[j];
       sh.cache[w] = (f == ~0ull) ? 0ull : f;
       known |= (f != ~0ull && f != 0ull);
@@ -284,63 +299,92 @@ __global__ void __launch_bounds__(kMergeThreads) dresd_merge(MergeParams p) {
   // (b), worth a selection only when some list's best key is known
   if (sh.any_known && G >= p.k) {
     const uint64_t t1 =
-        radix_kth(sh, [&](uint32_t i) { return sh.cache[i]; }, (uint32_t)G, (uint32_t)p.k);
+        radix_kth(sh, [&](uint32_t i) { return sh.cache[i]; }, (uint32_t)G, (uint32_t)p.k, 2);
     if (tid == 0 && t1 > sh.bound) sh.bound = t1;
   }
   __syncthreads();
   const uint64_t bnd = sh.bound;
 
-  // 2. offsets of the kept lists' keys (lists at or above the bound), then
-  //    every key loaded by its own thread
-  uint32_t mine = 0;
+  // 2. work items: 8 keys of a kept list (one whose best key reaches the
+  //    bound) for 8 lanes, so that short lists fill the loads too; 64 keys for
+  //    a wave where items of 8 would be too many.  In any order, eight rounds
+  //    of the workgroup in flight.
+  uint32_t items = 0;  // of 8 keys (low half) and of 64 (high half)
 #pragma unroll
   for (int j = 0; j < kListsPerThread; ++j) {
     if (first[j] < bnd) cnt[j] = 0;
-    mine += cnt[j];
+    items += (cnt[j] + 7u) / 8u + ((cnt[j] + 63u) / 64u << 16);
   }
-  uint32_t incl = mine;
+  uint32_t lo = items & 0xffffu, hi = items >> 16;
   for (int off = 1; off < kWaveSize; off <<= 1) {
-    const uint32_t v = __shfl_up(incl, off, kWaveSize);
-    if (lane >= off) incl += v;
-  }
-  if (lane == kWaveSize - 1) sh.part[wid] = incl;
-  __syncthreads();
-  uint32_t base = incl - mine;
-  for (int q = 0; q < wid; ++q) base += sh.part[q];
-#pragma unroll
-  for (int j = 0; j < kListsPerThread; ++j) {
-    sh.hist[tid * kListsPerThread + j] = base;
-    base += cnt[j];
-  }
-  if (tid == nth - 1) sh.total = base;
-  __syncthreads();
-  const uint32_t total = sh.total;
-  const int nl = G;
-  constexpr int R = 8;  // keys per thread per round, loaded together
-  for (uint32_t i0 = tid; i0 < total; i0 += R * nth) {
-    uint64_t key[R];
-#pragma unroll
-    for (int u = 0; u < R; ++u) {
-      const uint32_t i = i0 + (uint32_t)(u * nth);
-      key[u] = 0ull;
-      if (i < total) {
-        // the last list whose offset is <= i holds key i
-        int lo = 0, hi = nl;  // answer in [lo, hi)
-        while (hi - lo > 1) {
-          const int mid = (lo + hi) >> 1;
-          if (sh.hist[mid] <= i) lo = mid;
-          else hi = mid;
-        }
-        key[u] = lists[(size_t)lo * p.C + (i - sh.hist[lo])];
-      }
+    const uint32_t v = __shfl_up(lo, off, kWaveSize), h = __shfl_up(hi, off, kWaveSize);
+    if (lane >= off) {
+      lo += v;
+      hi += h;
     }
+  }
+  uint32_t base8 = 0, base64 = 0;
+  if (lane == kWaveSize - 1 && lo) {
+    base8 = atomicAdd(&sh.total8, lo);
+    base64 = atomicAdd(&sh.total64, hi);
+  }
+  base8 = __shfl(base8, kWaveSize - 1, kWaveSize) + lo - (items & 0xffffu);
+  base64 = __shfl(base64, kWaveSize - 1, kWaveSize) + hi - (items >> 16);
+  __syncthreads();
+  const bool small = sh.total8 <= kMergeItems;
+  const uint32_t total = small ? sh.total8 : sh.total64;
+  const int lg = small ? 3 : 6;  // keys per item, as a power of two
+  const uint32_t per = 1u << lg;
+  if (total <= kMergeItems) {
+    uint32_t at = small ? base8 : base64;
 #pragma unroll
-    for (int u = 0; u < R; ++u) {
-      if (i0 + (uint32_t)(u * nth) < total && key[u] >= bnd) {
-        const uint32_t at = atomicAdd(&sh.ncand, 1u);
-        if (at < (uint32_t)kMergeCap) sh.cache[at] = key[u];
-        else if ((int64_t)(at - kMergeCap) < p.spill_cap) spill[at - kMergeCap] = key[u];
+    for (int j = 0; j < kListsPerThread; ++j)
+      for (uint32_t c = 0; c < cnt[j]; c += per, ++at)
+        // list (12 bits), item of it (8), keys of the item - 1 (6)
+        sh.hist[at] = (uint32_t)(tid + j * kMergeThreads) | (c >> lg) << 12 |
+                      (min(cnt[j] - c, per) - 1u) << 20;
+  }
+  __syncthreads();
+  // a key at or above the bound becomes a candidate
+  auto offer = [&](uint64_t key) {
+    const bool take = key >= bnd && key != 0ull;
+    const uint64_t mk = __ballot(take);
+    if (!mk) return;
+    uint32_t at = 0;
+    if (lane == 0) at = atomicAdd(&sh.ncand, (uint32_t)__popcll(mk));
+    at = __builtin_amdgcn_readfirstlane(at) + (uint32_t)__popcll(mk & ((1ull << lane) - 1ull));
+    if (take) {
+      if (at < (uint32_t)kMergeCap) sh.cache[at] = key;
+      else if ((int64_t)(at - kMergeCap) < p.spill_cap) spill[at - kMergeCap] = key;
+    }
+  };
+  constexpr uint32_t NW = kMergeThreads / kWaveSize;
+  if (total <= kMergeItems) {
+    constexpr int R = 8;
+    const uint32_t round = (uint32_t)kMergeThreads >> lg;  // items of one round
+    const uint32_t mine = (uint32_t)tid >> lg, e = (uint32_t)tid & (per - 1u);
+    // (whole waves stay together: the loop bound is the workgroup's)
+    for (uint32_t i0 = 0; i0 < total; i0 += R * round) {
+      uint64_t key[R];
+#pragma unroll
+      for (int u = 0; u < R; ++u) {
+        const uint32_t i = i0 + (uint32_t)u * round + mine;
+        key[u] = 0ull;
+        if (i < total) {
+          const uint32_t it = sh.hist[i];
+          if (e <= it >> 20)
+            key[u] = lists[(size_t)(it & 4095u) * p.C + (((it >> 12) & 255u) << lg) + e];
+        }
       }
+#pragma unroll
+      for (int u = 0; u < R; ++u) offer(key[u]);
+    }
+  } else {  // more keys than items fit: every list in turn
+    for (int w = wid; w < G; w += (int)NW) {
+      if (lfirst[w] < bnd) continue;
+      const uint32_t n = min(lcnt[w] & ~kSortedFlag, (uint32_t)p.C);
+      for (uint32_t c = 0; c < n; c += kWaveSize)
+        offer(c + (uint32_t)lane < n ? lists[(size_t)w * p.C + c + lane] : 0ull);
     }
   }
   // Winner slots start empty (key 0 names no row), so that a slot no key
