@@ -12,7 +12,7 @@
 // the workgroup has) compare the hash with those of all earlier ranks (exact
 // comparison on a hash match), a workgroup prefix sum over the kept flags
 // gives every kept draft its row, and its T threads write it.  k = 100, L = 10:
-// 18.1 us with one thread per rank and the tokens in global memory, @DRAFTS@.
+// 5.4 us (18.1 with one thread per rank and the tokens in global memory).
 #include "dresd_device.h"
 #include "dresd_ops.h"
 

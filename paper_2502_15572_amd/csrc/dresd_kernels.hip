@@ -527,6 +527,7 @@ __device__ void parts_segments(const int64_t *probes, const int32_t *part_tile, 
   }
   __syncthreads();
   const int last = min(S, t * E + E - 1);  // earlier entries of this thread's last one
+#pragma unroll 8
   for (int i = 0; i < last; ++i) {
     const int32_t o = tile[i];
 #pragma unroll
@@ -564,11 +565,120 @@ __device__ void parts_segments(const int64_t *probes, const int32_t *part_tile, 
   __syncthreads();
 }
 
+// Partitioned search whose waves' lists hold every slot of their tiles (at
+// most C / 16 tiles each): no stage, threshold or cut.  Short streams are bounded
+// by latency, so a wave takes four tiles at a time with everything it reads for
+// them (slot rows, filter tokens, 16 key blocks) in flight at once instead of a
+// slot-row read behind each tile, and its keys leave the registers as one
+// unsorted list whose best key the merge prunes with.  The query's parts
+// repeat in all four row groups of the operand, so lane (g, m) finds the score
+// of row m of the group's tile g in that tile's accumulator: the same products
+// in the same order as scan_body.
+// Measured at B = 1: @SHORT@
+template <int DT, int CPQ>
+__device__ __forceinline__ void scan_few_tiles(const ScanParams &p, int gw, const int32_t *seg_off,
+                                               const int32_t *seg_tile, int64_t vtot,
+                                               unsigned char *smem) {
+  constexpr int EPC = (DT == kF32) ? 4 : 8;
+  const int lane = threadIdx.x & 63, g = lane >> 4, m = lane & 15;
+  const int KB = p.KB;
+  const int64_t v0 = wave_uniform(vtot * gw / p.G), v1 = wave_uniform(vtot * (gw + 1) / p.G);
+  const int nt = (int)(v1 - v0);
+  // The query's operand: chunk (kb, g, h) for part h.
+  for (int e = threadIdx.x; e < CPQ * KB * 4; e += blockDim.x) {
+    const int h = e / (KB * 4), r = e - h * (KB * 4);
+    *reinterpret_cast<u4 *>(smem + ((size_t)r * CPQ + h) * 16) =
+        query_chunk<DT, CPQ>(p.queries, p.d, 1, h, (r >> 2) * 4 * EPC + (r & 3) * EPC);
+  }
+  __syncthreads();
+  const int part = m & 3;
+  const unsigned char *qa = smem + ((size_t)g * CPQ + (part < CPQ ? part : 0)) * 16;
+  auto operand = [&](int kb) -> u4 {
+    const u4 a = *reinterpret_cast<const u4 *>(qa + (size_t)kb * 4 * CPQ * 16);
+    return part < CPQ ? a : u4{0, 0, 0, 0};
+  };
+  uint64_t *list = p.lists + (size_t)gw * p.C;
+  uint64_t best = 0;
+  for (int t0 = 0; t0 < nt; t0 += 4) {
+    // This lane group's tile (the wave's last one past its end): its segment
+    // is the first that ends past it.
+    const int32_t v = (int32_t)(v0 + (t0 + g < nt ? t0 + g : nt - 1));
+    int lo = 0, hi = p.S - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (seg_off[mid + 1] > v) hi = mid;
+      else lo = mid + 1;
+    }
+    const int32_t tile = seg_tile[lo] + (v - seg_off[lo]);
+    const int64_t slot = (int64_t)tile * kTileRows + m;
+    const uint32_t row = p.slot_row[slot];
+    const int32_t first_tok = p.ftok ? p.ftok[slot] : 0;
+    const u4 *base[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      base[t] = static_cast<const u4 *>(p.data) +
+                (int64_t)__builtin_amdgcn_readlane(tile, t * 16) * KB * 64 + lane;
+    f4 acc[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+    int kb = 0;
+    for (; kb + 4 <= KB; kb += 4) {
+      u4 blk[4][4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) blk[u][t] = __builtin_nontemporal_load(base[t] + (kb + u) * 64);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const u4 a = operand(kb + u);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t] = Mfma<DT>::run(a, blk[u][t], acc[t]);
+      }
+    }
+    for (; kb < KB; ++kb) {
+      u4 blk[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) blk[t] = __builtin_nontemporal_load(base[t] + kb * 64);
+      const u4 a = operand(kb);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[t] = Mfma<DT>::run(a, blk[t], acc[t]);
+    }
+    f4 s = acc[0];
+#pragma unroll
+    for (int t = 1; t < 4; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[i] = g == t ? acc[t][i] : s[i];
+    float sc = s[0];
+    if (CPQ == 4) {
+      const float s1 = (DT == kF16) ? (1.0f / 2048.0f) : 1.0f;
+      const float s2 = (DT == kF16) ? (1.0f / 4194304.0f) : 1.0f;
+      sc = (sc + s[1] * s1) + s[2] * s2;
+    }
+    // (a NaN score competes nowhere; key 0 is no candidate)
+    const bool in = t0 + g < nt && row != kPadRow && sc == sc &&
+                    (!p.ftok || first_tok == *p.next_tok);
+    const uint64_t key = in ? make_key(sc, row) : 0ull;
+    list[t0 * kTileRows + lane] = key;
+    best = key > best ? key : best;
+  }
+#pragma unroll
+  for (int off = 1; off < kWaveSize; off <<= 1) {
+    const uint64_t other = __shfl_xor(best, off, kWaveSize);
+    best = other > best ? other : best;
+  }
+  if (lane == 0) {
+    p.lcnt[gw] = best ? (uint32_t)((nt + 3) / 4 * kWaveSize) : 0u;
+    p.lfirst[gw] = best;
+    p.lkth[gw] = 0;
+  }
+}
+
 // Partitioned search (its own kernel name, so that profiles separate it from
 // the exact search): workgroup blockIdx.x serves query blockIdx.x / wgq, and
 // its waves own lists [G] of that query; otherwise it is a one-query scan.
+// Four waves per SIMD (at most 128 registers): the grid is four workgroups per CU.
 template <int DT, int CPQ>
-__global__ void __launch_bounds__(kScanThreads) dresd_scan_parts(ScanParams p) {
+__global__ void __launch_bounds__(kScanThreads, 4) dresd_scan_parts(ScanParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int qb = blockIdx.x / p.wgq;
   const int gw = (blockIdx.x - qb * p.wgq) * (blockDim.x >> 6) +
@@ -585,10 +695,17 @@ __global__ void __launch_bounds__(kScanThreads) dresd_scan_parts(ScanParams p) {
     int32_t *off = reinterpret_cast<int32_t *>(smem + p.seg_lds);
     int32_t *tile = off + p.S + 1;
     parts_segments(p.probes64 + (size_t)qb * p.S, p.part_tile, p.S, p.P, off, tile);
-    scan_body<DT, 1, CPQ, kModeParts>(q, gw, off, tile);
+    if (off[p.S] <= (int64_t)p.G * (p.C / kWaveSize * 4))  // (the same for all waves of the query)
+      scan_few_tiles<DT, CPQ>(q, gw, off, tile, off[p.S], smem);
+    else
+      scan_body<DT, 1, CPQ, kModeParts>(q, gw, off, tile);
   } else {
-    scan_body<DT, 1, CPQ, kModeParts>(q, gw, p.seg_off + (size_t)qb * (p.S + 1),
-                                      p.seg_tile + (size_t)qb * p.S);
+    const int32_t *off = p.seg_off + (size_t)qb * (p.S + 1);
+    const int32_t *tile = p.seg_tile + (size_t)qb * p.S;
+    if (off[p.S] <= (int64_t)p.G * (p.C / kWaveSize * 4))
+      scan_few_tiles<DT, CPQ>(q, gw, off, tile, off[p.S], smem);
+    else
+      scan_body<DT, 1, CPQ, kModeParts>(q, gw, off, tile);
   }
 }
 

@@ -1374,7 +1374,8 @@ dresd_status parts_search(dresd_ivf *v, const float *queries, const int64_t *pro
   int64_t wgq = std::min<int64_t>(ceil_div(4LL * ix->cus, B), ceil_div(avg_tiles, 16));
   wgq = std::max<int64_t>(1, std::min<int64_t>(wgq, kMergeLists / 4));
   const int G = (int)wgq * (kScanThreads / kWaveSize);
-  const int64_t spill_cap = std::max<int64_t>(0, (int64_t)G * k - kMergeCap);
+  // (a wave of few tiles lists all their slots, up to C keys)
+  const int64_t spill_cap = std::max<int64_t>(0, (int64_t)G * C - kMergeCap);
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   const size_t nb = (size_t)B;
   const size_t off_seg = 0;
