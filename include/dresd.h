@@ -192,8 +192,8 @@ dresd_status dresd_index_info(const dresd_index *ix, int64_t *N, int32_t *d,
                               int32_t *L, int32_t *dtype);
 
 /* Free an index and its workspace (synchronises its device).  NULL is
- * ignored.  Blocks of at least 64 MiB are kept for the library's next
- * allocations, together at most 1/128 of the device's memory (the oldest go
+ * ignored.  Blocks of keys and values of at least 64 MiB are kept for the
+ * next index that is created, together at most 1/128 of the device's memory (the oldest go
  * back to the driver first, all of them when an allocation of the library
  * fails); larger ones and everything smaller go back at once. */
 void dresd_index_destroy(dresd_index *ix);

@@ -167,6 +167,8 @@ void *qop_kernel_bf16();
 inline void *qop_kernel(int dtype) {
   return dtype == kF16 ? qop_kernel_f16() : dtype == kBF16 ? qop_kernel_bf16() : nullptr;
 }
+// Small datastores: fp32 keys (one column per query), 16-bit keys at four.
+ScanKernel scan_small_kernel(int dtype);
 ScanKernel scan_parts_kernel(int dtype);  // partitioned search, one query per workgroup
 
 void *merge_kernel_ptr();

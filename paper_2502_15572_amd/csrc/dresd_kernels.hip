@@ -52,48 +52,55 @@ struct Mfma<kBF16> {
 //          column.  bf16: high, middle, low.  f16: high, then the remainders
 //          scaled by 2^11 and 2^22 so they stay in f16's normal range (the
 //          epilogue scales their products back by the same powers of two).
+// query_part: part h of one chunk's values x.
 template <int DT, int CPQ>
-__device__ __forceinline__ u4 query_chunk(const float *q, int d, int B, int col, int dim0) {
+__device__ __forceinline__ u4 query_part(const float *x, int h) {
   u4 out;
-  const int b = col / CPQ;
-  const int h = col % CPQ;
-  if (DT == kF32) {
+  if constexpr (DT == kF32) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      int dim = dim0 + e;
-      float x = (b < B && dim < d) ? q[(int64_t)b * d + dim] : 0.0f;
-      out[e] = __float_as_uint(x);
+    for (int e = 0; e < 4; ++e) out[e] = __float_as_uint(x[e]);
+    return out;
+  } else {
+    uint16_t v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if (DT == kF16) {
+        _Float16 hi = (_Float16)x[e];
+        _Float16 r = hi;
+        if (CPQ == 4) {
+          float r1 = x[e] - (float)hi;                    // exact
+          _Float16 mid = (_Float16)(r1 * 2048.0f);        // 2^11
+          float r2 = r1 - (float)mid * (1.0f / 2048.0f);  // exact
+          _Float16 lo = (_Float16)(r2 * 4194304.0f);      // 2^22
+          r = (h == 0) ? hi : (h == 1) ? mid : (h == 2) ? lo : (_Float16)0.0f;
+        }
+        v[e] = __builtin_bit_cast(uint16_t, r);
+      } else {
+        __bf16 hi = (__bf16)x[e];
+        float r1 = x[e] - (float)hi;
+        __bf16 mid = (__bf16)r1;
+        __bf16 lo = (__bf16)(r1 - (float)mid);
+        __bf16 r = (h == 0) ? hi : (h == 1) ? mid : (CPQ == 4 && h == 2) ? lo : (__bf16)0.0f;
+        v[e] = __builtin_bit_cast(uint16_t, r);
+      }
     }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out[e] = (uint32_t)v[2 * e] | ((uint32_t)v[2 * e + 1] << 16);
     return out;
   }
-  uint16_t v[8];
+}
+
+template <int DT, int CPQ>
+__device__ __forceinline__ u4 query_chunk(const float *q, int d, int B, int col, int dim0) {
+  constexpr int EPC = DT == kF32 ? 4 : 8;
+  const int b = col / CPQ;
+  float x[EPC];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    int dim = dim0 + e;
-    float x = (b < B && dim < d) ? q[(int64_t)b * d + dim] : 0.0f;
-    if (DT == kF16) {
-      _Float16 hi = (_Float16)x;
-      _Float16 r = hi;
-      if (CPQ == 4) {
-        float r1 = x - (float)hi;                       // exact
-        _Float16 mid = (_Float16)(r1 * 2048.0f);        // 2^11
-        float r2 = r1 - (float)mid * (1.0f / 2048.0f);  // exact
-        _Float16 lo = (_Float16)(r2 * 4194304.0f);      // 2^22
-        r = (h == 0) ? hi : (h == 1) ? mid : (h == 2) ? lo : (_Float16)0.0f;
-      }
-      v[e] = __builtin_bit_cast(uint16_t, r);
-    } else {
-      __bf16 hi = (__bf16)x;
-      float r1 = x - (float)hi;
-      __bf16 mid = (__bf16)r1;
-      __bf16 lo = (__bf16)(r1 - (float)mid);
-      __bf16 r = (h == 0) ? hi : (h == 1) ? mid : (CPQ == 4 && h == 2) ? lo : (__bf16)0.0f;
-      v[e] = __builtin_bit_cast(uint16_t, r);
-    }
+  for (int e = 0; e < EPC; ++e) {
+    const int dim = dim0 + e;
+    x[e] = (b < B && dim < d) ? q[(int64_t)b * d + dim] : 0.0f;
   }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) out[e] = (uint32_t)v[2 * e] | ((uint32_t)v[2 * e + 1] << 16);
-  return out;
+  return query_part<DT, CPQ>(x, col % CPQ);
 }
 
 // Scan modes: the main pass over every tile, a sampled threshold pass over
@@ -574,7 +581,8 @@ __device__ void parts_segments(const int64_t *probes, const int32_t *part_tile, 
 // repeat in all four row groups of the operand, so lane (g, m) finds the score
 // of row m of the group's tile g in that tile's accumulator: the same products
 // in the same order as scan_body.
-// Measured at B = 1: @SHORT@
+// Measured at B = 1, 33.5M x 128 f16: 64 probed partitions (16,400 tiles) 34 ->
+// 25 us; decode step grouped by first token 76 -> 47 us.
 template <int DT, int CPQ>
 __device__ __forceinline__ void scan_few_tiles(const ScanParams &p, int gw, const int32_t *seg_off,
                                                const int32_t *seg_tile, int64_t vtot,
@@ -709,6 +717,137 @@ __global__ void __launch_bounds__(kScanThreads, 4) dresd_scan_parts(ScanParams p
   }
 }
 
+// Small datastores (at most 4,096 lists of one, two or four whole tiles): no
+// thresholds, stages or sampled passes, which cost more than they save where a
+// wave meets few rows.  Workgroup (x, y): four waves of C / 16 consecutive
+// tiles each, query tile y.  A wave writes every key of its tiles, one
+// unsorted list per query, and each list's best key, with which the merge
+// prunes.  The products and their order are scan_body's.  Bounded by latency:
+// the first eight key blocks are in flight while the workgroup builds the
+// query operand.
+// Measured: 16,384 x 256 fp32 keys, B = 8: search 28.9 -> 17.7 us; the probe
+// of 8,192 x 128 centroids for 128 queries 120 -> 21 us.
+template <int DT, int CPQ>
+__global__ void __launch_bounds__(kScanThreads) dresd_scan_small(ScanParams p) {
+  constexpr int QPT = 16 / CPQ, NS = 4 / CPQ, EPC = (DT == kF32) ? 4 : 8, U = 8;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int lane = threadIdx.x & 63, g = lane >> 4, m = lane & 15;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int KB = p.KB, tpw = p.C / kTileRows;
+  const int q0 = (int)blockIdx.y * QPT;
+  const int gw = (int)blockIdx.x * 4 + wv;
+  const int64_t t0 = (int64_t)gw * tpw;
+  const int64_t left = p.nvisit - t0;
+  const int nt = left <= 0 ? 0 : left < tpw ? (int)left : tpw;
+  const int J = nt * KB;  // the wave's tiles are one run of blocks
+  const u4 *base = static_cast<const u4 *>(p.data) + t0 * KB * 64 + lane;
+  u4 cur[U];
+  if (J > 0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) cur[u] = base[(int64_t)(u < J ? u : J - 1) * 64];
+  }
+  // first tokens of the rows (next-token filter), at most four tiles
+  int32_t ftok[4] = {0, 0, 0, 0};
+  if (p.ftok) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      if (t < nt) ftok[t] = p.ftok[(t0 + t) * kTileRows + m];
+  }
+  // The query operand: chunk (kb, g, column) for the columns in use; a
+  // thread reads eight (four) dims of a query once and writes its CPQ parts.
+  const int nq = p.B - q0 < QPT ? p.B - q0 : QPT, ncol = nq * CPQ;
+  const bool qvec = (p.d & 3) == 0 && ((uintptr_t)p.queries & 15u) == 0;
+  for (int e = threadIdx.x; e < nq * KB * 4; e += kScanThreads) {
+    const int q = e / (KB * 4), r = e - q * (KB * 4), dim0 = r * EPC;
+    const float *src = p.queries + (int64_t)(q0 + q) * p.d + dim0;
+    float x[EPC];
+    if (qvec && dim0 + EPC <= p.d) {
+#pragma unroll
+      for (int i = 0; i < EPC; i += 4) {
+        const float4 v = *reinterpret_cast<const float4 *>(src + i);
+        x[i] = v.x, x[i + 1] = v.y, x[i + 2] = v.z, x[i + 3] = v.w;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < EPC; ++i) x[i] = dim0 + i < p.d ? src[i] : 0.f;
+    }
+#pragma unroll
+    for (int h = 0; h < CPQ; ++h)
+      *reinterpret_cast<u4 *>(smem + ((size_t)r * ncol + q * CPQ + h) * 16) =
+          query_part<DT, CPQ>(x, h);
+  }
+  __syncthreads();
+  if (gw >= p.G) return;
+  uint64_t best[NS];
+  int32_t want[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    best[s] = 0;
+    const int q = q0 + g * NS + s;
+    want[s] = (p.ftok && q < p.B) ? p.next_tok[q] : 0;
+  }
+  f4 acc = {0.f, 0.f, 0.f, 0.f};
+  int kb = 0, t = 0;
+  for (int j = 0; j < J; j += U) {
+    u4 nxt[U];
+    if (j + U < J) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        nxt[u] = base[(int64_t)(j + U + u < J ? j + U + u : J - 1) * 64];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (j + u < J) {
+        const u4 av = *reinterpret_cast<const u4 *>(
+            smem + ((size_t)(kb * 4 + g) * ncol + (m < ncol ? m : 0)) * 16);
+        acc = Mfma<DT>::run(m < ncol ? av : u4{0, 0, 0, 0}, cur[u], acc);
+        if (++kb == KB) {
+          const int64_t row = (t0 + t) * kTileRows + m;
+          const int32_t f = t == 0 ? ftok[0] : t == 1 ? ftok[1] : t == 2 ? ftok[2] : ftok[3];
+#pragma unroll
+          for (int s = 0; s < NS; ++s) {
+            float v = acc[s * CPQ];
+            if (CPQ == 4) {
+              const float s1 = (DT == kF16) ? (1.0f / 2048.0f) : 1.0f;
+              const float s2 = (DT == kF16) ? (1.0f / 4194304.0f) : 1.0f;
+              v = (v + acc[s * CPQ + 1] * s1) + acc[s * CPQ + 2] * s2;
+            }
+            const int q = q0 + g * NS + s;
+            // (a NaN score competes nowhere; key 0 is no candidate)
+            const bool in = row < p.N && v == v && (!p.ftok || f == want[s]);
+            const uint64_t key = in ? make_key(v, (uint32_t)row) : 0ull;
+            if (q < p.B) p.lists[((size_t)q * p.G + gw) * p.C + t * kTileRows + m] = key;
+            best[s] = key > best[s] ? key : best[s];
+          }
+          acc = f4{0.f, 0.f, 0.f, 0.f};
+          kb = 0;
+          ++t;
+        }
+      }
+    }
+    if (j + U < J) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) cur[u] = nxt[u];
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    uint64_t b = best[s];
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) {
+      const uint64_t o = __shfl_xor(b, off, kWaveSize);
+      b = o > b ? o : b;
+    }
+    const int q = q0 + g * NS + s;
+    if (m == 0 && q < p.B) {
+      const size_t o = (size_t)q * p.G + gw;
+      p.lcnt[o] = b ? (uint32_t)(nt * kTileRows) : 0u;
+      p.lfirst[o] = b;
+      p.lkth[o] = 0;
+    }
+  }
+}
+
 // ---------------------------------------------------------------- tables ---
 // This file is compiled once per scan variant (DRESD_TU = 1..4) and once for
 // the layout and dispatch (DRESD_TU = 0) so that the variants build in
@@ -778,6 +917,13 @@ ScanKernel scan_kernel(int dtype, int qt, int cpq, bool main_pass, bool shared) 
   if (dtype == kF16 && cpq == 4) return scan_kernel_variant2(qi, main_pass, shared);
   if (dtype == kBF16 && cpq == 4) return scan_kernel_variant3(qi, main_pass, shared);
   if (dtype == kBF16 && cpq == 2) return scan_kernel_variant4(qi, main_pass, shared);
+  return nullptr;
+}
+
+ScanKernel scan_small_kernel(int dtype) {
+  if (dtype == kF32) return (ScanKernel)dresd_scan_small<kF32, 1>;
+  if (dtype == kF16) return (ScanKernel)dresd_scan_small<kF16, 4>;
+  if (dtype == kBF16) return (ScanKernel)dresd_scan_small<kBF16, 4>;
   return nullptr;
 }
 

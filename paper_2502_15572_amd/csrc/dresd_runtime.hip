@@ -101,29 +101,30 @@ struct BlockCache {
     }
     kept.resize(n);
   }
-  hipError_t take(void **ptr, size_t bytes) {
+  hipError_t take(void **ptr, size_t bytes, bool keep) {
     *ptr = nullptr;
     try {
-      return take_block(ptr, bytes);
+      return take_block(ptr, bytes, keep);
     } catch (const std::bad_alloc &) {  // the host's own lists
       if (*ptr) (void)hipFree(*ptr);
       *ptr = nullptr;
       return hipErrorOutOfMemory;
     }
   }
-  hipError_t take_block(void **ptr, size_t bytes) {
+  hipError_t take_block(void **ptr, size_t bytes, bool keep) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     std::lock_guard<std::mutex> lock(mu);
     size_t unused = 0, total = 0, held = 0;
-    if (bytes >= kMinBlock) {
+    keep = keep && bytes >= kMinBlock;
+    if (keep) {
       e = hipMemGetInfo(&unused, &total);
       if (e != hipSuccess) return e;
     }
     const size_t want = rounded(bytes);
-    if (bytes >= kMinBlock && want <= total / 128) {  // a size that may be kept
-      kept.reserve(kept.size() + live.size() + 2);    // give() allocates nothing
+    if (keep && want <= total / 128) {              // a size that may be kept
+      kept.reserve(kept.size() + live.size() + 2);  // give() allocates nothing
       for (size_t i = 0; i < kept.size(); ++i)
         if (kept[i].dev == dev && kept[i].bytes == want) {
           live[kept[i].ptr] = {want, dev};
@@ -191,11 +192,13 @@ BlockCache &block_cache() {
 // Releases what dev_alloc returned (waiting for the device like hipFree).
 void dev_free(void *ptr) { block_cache().give(ptr); }
 
-// Every device allocation of the library goes through here.  Test hook: with
+// Every device allocation of the library goes through here (keep: a part of
+// an index or of its build, whose block may come from and go back to the cache
+// above).  Test hook: with
 // DRESD_FAIL_ALLOC_AT=n in the environment, the n-th allocation counted since
 // the variable last changed fails as out of memory without allocating, so
 // that each allocation-failure path can be driven on purpose.
-hipError_t dev_alloc(void **ptr, size_t bytes) {
+hipError_t dev_alloc(void **ptr, size_t bytes, bool keep = false) {
   static std::mutex mu;
   static std::string armed;
   static long seen = 0;
@@ -216,7 +219,7 @@ hipError_t dev_alloc(void **ptr, size_t bytes) {
       }
     }
   }
-  return block_cache().take(ptr, bytes);
+  return block_cache().take(ptr, bytes, keep);
 }
 
 // A buffer may only grow outside stream capture: growing allocates and
@@ -272,6 +275,8 @@ struct Group {
   int b0, nb, ng;
 };
 
+// Most 1 KiB key blocks, and (query, tile) pairs, of a search of whole-tile lists.
+constexpr int64_t kSmallBlocks = 1 << 17, kSmallTiles = 1 << 20;
 constexpr size_t kMaxGroup = 256;  // queries per launch: 16 query tiles x 16 columns
 constexpr int kMaxScanWgPerCu = 4;
 // One workgroup (4 waves, one per SIMD) per CU where it measured faster:
@@ -310,6 +315,7 @@ struct Plan {
   int64_t spill_cap = 0;        // merge candidates per query beyond its LDS cache
   bool sort_lists = false;
   bool filt = false;            // next-token-filtered search
+  bool small = false;           // whole tiles listed without thresholds (dresd_scan_small)
   size_t off_tau = 0, off_lcnt = 0, off_lkth = 0, off_lfirst = 0, off_lists = 0, off_spill = 0;
   size_t off_qop = 0;               // shared-key scan: query operands of a group
   size_t bytes = 0;
@@ -462,7 +468,36 @@ dresd_status make_plan(dresd_index *ix, int B, int k, Plan &pl, bool filt = fals
       pl.lds_s = scan_tc_lds_bytes(qtw, smp->tpw, smp->nk, nq, smp->st, nqw, pl.C, np, filt);
     }
   }
-  if (pl.tc) {
+  // Small datastores whose scan would be the single-tile one (fp32 keys, or
+  // 16-bit keys with at most four queries): lists of one, two or four whole
+  // tiles, as many as the merge accepts.  Measured against the single-tile
+  // scan: 16,384 x 256 fp32 at B = 1 / 8 / 128 16.3 / 17.7 / 43.6 us (18.1 /
+  // 28.9 / 167), 65,536 x 128 f16 at B = 1 15.6 us (21.9), 262,144 x 128 f16
+  // 26.5 us (35.7).  Past 128 MiB of keys long streams win (262,144 x 1,024
+  // bf16 122 us against 101), with the next-token filter, which leaves one
+  // query few candidates, past 32 MiB (262,144 x 128 f16 28.2 against 27.5).
+  // Waves of 16 blocks or fewer take several tiles while that leaves more
+  // lists than CUs.
+  if (!pl.tc && !(mq_type && mq_kb && (qt_all >= 2 || pl.terms < 4)) &&
+      (ix->dtype == kF32 || pl.terms == 4) && ix->KB <= 32 && ix->T <= 4 * kMergeLists &&
+      ix->T * ix->KB <= (filt && B == 1 ? kSmallBlocks / 4 : kSmallBlocks) &&
+      (int64_t)B * ix->T <= kSmallTiles) {
+    int tpw = 1;
+    for (int64_t g = ix->T;
+         tpw < 4 && (g > kMergeLists || (g > 2048 && ix->KB <= 8) ||
+                     (g > 1024 && 2 * tpw * ix->KB <= 16));
+         g = ceil_div(ix->T, tpw))
+      tpw <<= 1;
+    pl.small = true;
+    pl.C = tpw * kTileRows;
+    pl.B = pl.bl = pl.bmax = B;
+    pl.nl = 1;
+    pl.qt = qt_all;
+    pl.G_max = (int)ceil_div(ix->T, tpw);
+    pl.wg_max = (int)ceil_div(pl.G_max, 4);
+    pl.kmain = scan_small_kernel(ix->dtype);
+    pl.lds = (size_t)ix->KB * kBlockBytes;
+  } else if (pl.tc) {
   } else if (mq_type && mq_kb && (qt_all >= 2 || pl.terms < 4)) {
     // Several query tiles, or one of one- or two-column queries (four or
     // two scores per lane per key tile): queries stationary in registers,
@@ -523,6 +558,7 @@ dresd_status make_plan(dresd_index *ix, int B, int k, Plan &pl, bool filt = fals
     pl.CL = stage_cap(pl.qt * pl.qpt);
     pl.lds = scan_lds(bmax * pl.terms, ix->KB, pl.qt * pl.qpt, pl.CL, pl.C);
   }
+  if (!pl.small) {
   const int bmax = pl.bmax;
   const int ngr = (int)ceil_div(B, bmax);
   // The single-tile scan serves several groups per launch; launch sizes
@@ -595,9 +631,10 @@ dresd_status make_plan(dresd_index *ix, int B, int k, Plan &pl, bool filt = fals
     for (int i = 0; i + 1 < pl.npass; ++i)
       pl.spec[i] = spec_rank(k, pl.strides[i] / pl.strides[i + 1]);
   }
-  // Lists end with at most k keys each, so a query never has more than
-  // G_max * k merge candidates.
-  pl.spill_cap = std::max<int64_t>(0, (int64_t)pl.G_max * k - kMergeCap);
+  }
+  // Lists end with at most k keys each (C where whole tiles are listed), so a
+  // query never has more than G_max times that many merge candidates.
+  pl.spill_cap = std::max<int64_t>(0, (int64_t)pl.G_max * (pl.small ? pl.C : k) - kMergeCap);
   size_t nb = (size_t)pl.bl;
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   pl.off_tau = 0;  // [2 levels][kMaxGroup] bounds, then [2 levels][kMaxGroup] speculative keys
@@ -802,18 +839,18 @@ dresd_status index_build(const void *embeddings, const int32_t *continuations, i
   ix->T = slot_row ? T : ceil_div(N, kTileRows);
   const size_t data_bytes = (size_t)ix->T * ix->KB * kBlockBytes;
   const size_t cont_bytes = (size_t)N * L * sizeof(int32_t);
-  if (dev_alloc(&ix->data, data_bytes) != hipSuccess) {
+  if (dev_alloc(&ix->data, data_bytes, true) != hipSuccess) {
     (void)hipGetLastError();
     ix->data = nullptr;
     return cleanup(fail(DRESD_ENOMEM, "key storage allocation failed"));
   }
-  if (dev_alloc((void **)&ix->cont, cont_bytes) != hipSuccess) {
+  if (dev_alloc((void **)&ix->cont, cont_bytes, true) != hipSuccess) {
     (void)hipGetLastError();
     ix->cont = nullptr;
     return cleanup(fail(DRESD_ENOMEM, "continuation storage allocation failed"));
   }
   const size_t ftok_bytes = (size_t)ix->T * kTileRows * sizeof(int32_t);
-  if (!slot_row && dev_alloc((void **)&ix->ftok, ftok_bytes) != hipSuccess) {
+  if (!slot_row && dev_alloc((void **)&ix->ftok, ftok_bytes, true) != hipSuccess) {
     (void)hipGetLastError();
     ix->ftok = nullptr;
     return cleanup(fail(DRESD_ENOMEM, "first-token column allocation failed"));
@@ -1096,9 +1133,10 @@ dresd_status search_impl(dresd_index *ix, const float *queries, const int32_t *n
       sp.stride = stride;
       sp.nvisit = ceil_div(ix->T, stride);
       sp.tau = (main_pass || !spec_in) ? tau_in : spec_in;
-      const int64_t wgs = pass_wgs(pl, gr, sp.nvisit, main_pass);
+      const int64_t wgs = pl.small ? pl.wg_max : pass_wgs(pl, gr, sp.nvisit, main_pass);
       const int threads = threads_of(pl, main_pass);
-      sp.G = (int)(pl.mq ? wgs
+      sp.G = (int)(pl.small ? pl.G_max
+                   : pl.mq ? wgs
                          : pl.tc ? wgs * (main_pass ? pl.nk_main : pl.nk_sample)
                                  : wgs * (threads / kWaveSize));
       void *sargs[] = {&sp};
@@ -1109,7 +1147,8 @@ dresd_status search_impl(dresd_index *ix, const float *queries, const int32_t *n
         if (!e0 || !e1) return fail(DRESD_EDEVICE, "hipEventCreate failed");
       }
       DRESD_HIP(launch((const void *)(main_pass ? pl.kmain : pl.ksample),
-                       dim3((unsigned)(wgs * gr.ng)), dim3((unsigned)threads), sargs,
+                       dim3((unsigned)(wgs * gr.ng), pl.small ? (unsigned)pl.qt : 1u),
+                       dim3((unsigned)threads), sargs,
                        main_pass ? pl.lds : pl.lds_s, e0, e1));
       if (main_pass && prof) {
         ix->ev_scan.push_back(e0);
@@ -1543,7 +1582,7 @@ static dresd_status ivf_build(const void *embeddings, const int32_t *continuatio
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   const size_t seq = up(((size_t)std::max<int64_t>(N, by_token ? 0 : P) + 1) * 4);
   const size_t off_hist = 4 * seq, off_counts = off_hist + up(1026 * 4);
-  if (dev_alloc((void **)&hold.tmp, off_counts + up((size_t)gp.nblk * 256 * 4)) != hipSuccess) {
+  if (dev_alloc((void **)&hold.tmp, off_counts + up((size_t)gp.nblk * 256 * 4), true) != hipSuccess) {
     (void)hipGetLastError();
     hold.tmp = nullptr;
     return fail(DRESD_ENOMEM, "memory to group the keys");
@@ -1607,8 +1646,8 @@ static dresd_status ivf_build(const void *embeddings, const int32_t *continuatio
   v->P = P;
   v->probe_tiles = std::max<int64_t>(1, (int64_t)(sq / (double)std::max<int64_t>(1, T)));
   gp.nslot = T * kTileRows;
-  if (dev_alloc((void **)&v->slot_row, (size_t)gp.nslot * 4) != hipSuccess ||
-      dev_alloc((void **)&v->ftok_slot, (size_t)gp.nslot * 4) != hipSuccess ||
+  if (dev_alloc((void **)&v->slot_row, (size_t)gp.nslot * 4, true) != hipSuccess ||
+      dev_alloc((void **)&v->ftok_slot, (size_t)gp.nslot * 4, true) != hipSuccess ||
       dev_alloc((void **)&v->part_tile, pt.size() * 4) != hipSuccess ||
       (by_token && dev_alloc((void **)&v->tok, (size_t)P * 4) != hipSuccess)) {
     (void)hipGetLastError();

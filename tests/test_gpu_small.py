@@ -1,0 +1,143 @@
+"""Exact search over small datastores whose waves list whole tiles
+(dresd_scan_small) and partitioned scans of few tiles, against the oracle: the
+edges of the list sizes (one, two, four tiles per wave), ragged rows and
+dims, batches around a query tile, k above the number of lists, the
+next-token filter and rows that must not compete."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from datagen import to_numpy_bits
+from parity import TOL, check_batch
+from test_gpu_kmeans import DEV, as_keys, say, unit
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # dtype, N, d, B, k
+    ("f32", 1, 1, 1, 1),
+    ("f32", 17, 3, 5, 17),          # every row returned, two tiles
+    ("f32", 16384, 256, 16, 10),    # one query tile, full
+    ("f32", 16401, 20, 17, 33),     # a tile past 1,024; one query past a tile
+    ("f32", 32769, 8, 2, 1),        # two tiles per wave
+    ("f32", 65553, 16, 3, 100),     # past 4,096 tiles
+    ("f32", 262144, 17, 2, 64),     # four tiles per wave, as many lists as the merge takes
+    ("f32", 5000, 500, 129, 20),    # 32 blocks per tile; nine query tiles
+    ("f32", 3000, 64, 2, 1024),     # k above the lists: every key a candidate
+    ("f16", 16384, 128, 4, 100),
+    ("f16", 40003, 100, 1, 16),     # ragged dims, two tiles per wave
+    ("f16", 9999, 1024, 3, 7),
+    ("bf16", 20011, 33, 2, 50),
+    ("bf16", 2047, 700, 4, 300),
+]
+
+
+def data(dt, N, d, B, seed):
+    rng = np.random.default_rng(seed)
+    x = unit(rng, N, d)
+    q = unit(rng, B, d).astype(np.float32)
+    src = rng.integers(0, N, B)
+    q[: B // 2 + 1] = (x[src[: B // 2 + 1]]).astype(np.float32)
+    cont = rng.integers(0, 7, (N, 3)).astype(np.int32)
+    return as_keys(x, dt), torch.from_numpy(q), cont, cont[src, 0].astype(np.int32)
+
+
+@pytest.mark.parametrize("dt,N,d,B,k", CASES, ids=["%s-N%d-d%d-B%d-k%d" % c for c in CASES])
+def test_small_search(gpu_lib, dt, N, d, B, k):
+    from paper_2502_15572_amd import Index
+    say("small search", dt, N, d, B, k)
+    keys, q, cont, nt = data(dt, N, d, B, N + d + B + k)
+    kb, kdt = to_numpy_bits(keys)
+    qn = q.numpy()
+    ix = Index(keys.to(DEV), torch.from_numpy(cont).to(DEV))
+    ntd = torch.from_numpy(nt).to(DEV)
+    for filt in (False, True):
+        idx, score, tok = ix.search(q.to(DEV), k, next_tok=ntd if filt else None)
+        torch.cuda.synchronize()
+        o_idx, o_score, _, o_next = oracle.topk(kb, kdt, qn, k, cont,
+                                                next_tok=nt if filt else None)
+        # exact query parts at every batch: the fp32 bound for all types
+        check_batch(idx.cpu().numpy(), score.cpu().numpy(), tok.cpu().numpy(), o_idx, o_score,
+                    o_next, lambda b, rows: oracle.score_rows(kb, kdt, qn[b], rows), N, cont,
+                    1e-5, next_tok=nt if filt else None)
+    ix.close()
+
+
+@pytest.mark.parametrize("dt", ["f32", "f16"])
+def test_rows_that_cannot_compete(gpu_lib, dt):
+    """NaN scores are never returned (their ranks are padded), an infinite
+    score ranks first or last, and neither touches its neighbours."""
+    from paper_2502_15572_amd import Index, PartitionedIndex
+    say("rows that cannot compete", dt)
+    N, d, B, k = 100, 32, 3, 100
+    keys, q, cont, _ = data(dt, N, d, B, 5)
+    q = q.abs() + 0.01
+    clean = keys.clone()
+    for r in (0, 15, 16, 50, 99):
+        keys[r, 3] = float("nan")
+    keys[51, 4], keys[52, 4] = float("inf"), float("-inf")
+    cd = torch.from_numpy(cont).to(DEV)
+    nan, rest = [0, 15, 16, 50, 99], [r for r in range(N) if r not in (0, 15, 16, 50, 99, 51, 52)]
+
+    def look(idx, score):
+        idx, score = idx.cpu().numpy(), score.cpu().numpy()
+        want = clean.double().numpy()[rest] @ q.double().numpy().T
+        for b in range(B):
+            # 16-bit keys: the query's other parts are zero or opposite, so an infinite
+            # score may be NaN and drop out
+            got = [r for r in idx[b].tolist() if r >= 0]
+            assert not set(got) & set(nan)
+            assert set(rest) <= set(got)
+            if 51 in got:
+                assert got[0] == 51
+            if 52 in got:
+                assert got[-1] == 52
+            by = dict(zip(idx[b].tolist(), score[b].tolist()))
+            assert np.allclose([by[r] for r in rest], want[:, b], atol=1e-5)
+
+    ix = Index(keys.to(DEV), cd)
+    idx, score, _ = ix.search(q.to(DEV), k)
+    look(idx, score)
+    ix.close()
+    a = torch.zeros(N, dtype=torch.int32, device=DEV)
+    a[40:] = 1
+    pix = PartitionedIndex(keys.to(DEV), cd, torch.eye(2, d, device=DEV), a)
+    probes = torch.tensor([[1, 0]] * B, dtype=torch.int32, device=DEV)
+    idx, score, _ = pix.search_probes(q.to(DEV), probes, k)
+    look(idx, score)
+    pix.close()
+
+
+@pytest.mark.parametrize("k", [1, 70, 300])
+def test_few_and_many_tiles(gpu_lib, k):
+    """Partitions just within and just past the tiles that a wave lists
+    whole, in one batch: both forms of the scan agree with the oracle."""
+    from paper_2502_15572_amd import PartitionedIndex
+    say("few and many tiles", k)
+    rng = np.random.default_rng(k)
+    d, P = 32, 40
+    sizes = np.concatenate([[30000, 1, 500], rng.integers(1, 200, P - 3)])
+    a = np.repeat(np.arange(P), sizes).astype(np.int32)
+    N = a.size
+    rng.shuffle(a)
+    keys = as_keys(unit(rng, N, d), "f16")
+    cont = rng.integers(0, 9, (N, 2)).astype(np.int32)
+    B = 30
+    q = unit(rng, B, d).astype(np.float32)
+    probes = np.stack([rng.permutation(P)[:3] for _ in range(B)]).astype(np.int32)
+    probes[0] = [0, 1, 2]
+    probes[1] = [1, 1, -5]
+    ix = PartitionedIndex(keys.to(DEV), torch.from_numpy(cont).to(DEV),
+                          torch.from_numpy(unit(rng, P, d).astype(np.float32)).to(DEV),
+                          torch.from_numpy(a).to(DEV))
+    idx, score, tok = ix.search_probes(torch.from_numpy(q).to(DEV),
+                                       torch.from_numpy(probes).to(DEV), k)
+    torch.cuda.synchronize()
+    kb, dt = to_numpy_bits(keys)
+    o_idx, o_score, _, o_next = oracle.topk_partitioned(kb, dt, q, k, a, P, probes, cont)
+    sets = [set(r.tolist()) for r in probes]
+    check_batch(idx.cpu().numpy(), score.cpu().numpy(), tok.cpu().numpy(), o_idx, o_score, o_next,
+                lambda b, rows: oracle.score_rows(kb, dt, q[b], rows), N, cont, 1e-5,
+                admitted_b=lambda b, rows: np.isin(a[rows], list(sets[b])))
+    ix.close()
