@@ -424,7 +424,8 @@ dresd_status dresd_ivf_search_next_token(dresd_ivf *ivf, const float *queries,
  *   order of the rows (deterministic).  x as above with n < 2^31; assign
  *   device [n] int32, each in [0, P) (not checked: the caller's contract);
  *   centroids device [P, d] fp32 in/out; counts device [P] int32 out (rows per
- *   centroid, NULL allowed).  Uses a workspace of P*d*8 + P*4 bytes per
+ *   centroid, NULL allowed).  Uses a workspace of P*d*8 + P*4 bytes (and, from
+ *   2^24 elements to 2^24 rows, where it can be had, 16 n more to sort them) per
  *   (device, stream), allocated (synchronously) on first use on that stream
  *   and kept, like every buffer it outgrows, until the process ends: calls
  *   on different streams may overlap, calls on one stream are ordered by it.

@@ -15,7 +15,8 @@
 //   update : each centroid becomes the unit vector along the sum of its
 //            rows (unchanged when it has none).  Rows are added into 64-bit
 //            fixed point (2^-30 units) with integer atomics, so the sums, and
-//            the centroids, do not depend on the order of the additions.
+//            the centroids, do not depend on the order of the additions.  Many
+//            rows are sorted by partition first (one atomic per run of rows).
 //   init   : the starting centroids, P distinct rows taken at even spacing
 //            through the row order from a seeded offset, each scaled to unit
 //            length.
@@ -263,6 +264,59 @@ __global__ void __launch_bounds__(256) dresd_kmeans_accumulate(KmeansParams p) {
   }
 }
 
+// The same sums over rows sorted by partition (dresd_group.hip): a wave adds 64
+// consecutive sorted rows in registers, 64 dims at a time, eight rows' loads in
+// flight, and adds to a partition's sum once per run of its rows: with 64 rows
+// per partition one atomic for about 30 of the unsorted kernel's, whose atomics
+// bound it.  Integer sums: the same result to the bit.
+template <int DT>
+__global__ void __launch_bounds__(256) dresd_kmeans_accumulate_sorted(KmeansParams p) {
+  const int lane = threadIdx.x & 63;
+  const int64_t w0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kWaveSize;
+  if (w0 >= p.n) return;
+  const int nr = (int)(p.n - w0 < kWaveSize ? p.n - w0 : kWaveSize);
+  const int64_t at = w0 + (lane < nr ? lane : nr - 1);
+  const uint32_t row = p.sorted_row[at];
+  const int32_t part = (int32_t)p.sorted_part[at];
+  // counts: the first lane of each run adds its length
+  const int32_t before = __shfl_up(part, 1, kWaveSize);
+  const bool head = lane < nr && (lane == 0 || before != part);
+  const uint64_t heads = __ballot(head);
+  if (head) {
+    const uint64_t later = lane == 63 ? 0ull : heads >> (lane + 1);
+    const int end = later ? lane + 1 + (__ffsll((long long)later) - 1) : nr;
+    atomicAdd(p.cnt + part, end - lane);
+  }
+  for (int j0 = 0; j0 < p.d; j0 += kWaveSize) {
+    const int j = j0 + lane;
+    const bool in = j < p.d;
+    long long acc = 0;
+    for (int r0 = 0; r0 < nr; r0 += 8) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int r = r0 + u < nr ? r0 + u : nr - 1;
+        const uint32_t src = __builtin_amdgcn_readlane(row, r);
+        v[u] = in ? load_elem<DT>(p.x, (int64_t)src * p.d + j) : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int r = r0 + u;
+        if (r >= nr) break;
+        acc += __double2ll_rn((double)v[u] * kFixScale);
+        const bool last = r + 1 == nr || ((heads >> (r + 1)) & 1ull);
+        if (last) {
+          const int32_t a = __builtin_amdgcn_readlane(part, r);
+          if (in && acc != 0)
+            atomicAdd(reinterpret_cast<unsigned long long *>(p.sums + (int64_t)a * p.d + j),
+                      (unsigned long long)acc);
+          acc = 0;
+        }
+      }
+    }
+  }
+}
+
 // One wave per partition: centroid = sum / ||sum|| when the partition has
 // rows and a non-zero sum; otherwise unchanged.
 __global__ void __launch_bounds__(256) dresd_kmeans_finish(KmeansParams p) {
@@ -339,7 +393,14 @@ hipError_t launch_kmeans_update(const KmeansParams &pin, int cus, hipStream_t st
   hipError_t e = launch1(dresd_kmeans_clear, blocks((int64_t)p.P * p.d + p.P, cus * 8LL),
                          dim3(256), p, st);
   if (e != hipSuccess) return e;
-  if (p.n > 0) {
+  if (p.n > 0 && p.sorted_row) {
+    const dim3 grid((unsigned)((p.n + 255) / 256));
+    if (p.dtype == kF32) e = launch1(dresd_kmeans_accumulate_sorted<kF32>, grid, dim3(256), p, st);
+    else if (p.dtype == kF16)
+      e = launch1(dresd_kmeans_accumulate_sorted<kF16>, grid, dim3(256), p, st);
+    else e = launch1(dresd_kmeans_accumulate_sorted<kBF16>, grid, dim3(256), p, st);
+    if (e != hipSuccess) return e;
+  } else if (p.n > 0) {
     const dim3 grid = blocks(p.n * p.d, cus * 32LL);
     if (p.dtype == kF32) e = launch1(dresd_kmeans_accumulate<kF32>, grid, dim3(256), p, st);
     else if (p.dtype == kF16) e = launch1(dresd_kmeans_accumulate<kF16>, grid, dim3(256), p, st);

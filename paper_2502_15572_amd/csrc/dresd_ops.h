@@ -127,6 +127,7 @@ struct KmeansParams {
   int32_t *counts;           // [P] out, may be null (update)
   long long *sums;           // [P, d] fixed-point workspace (update)
   int32_t *cnt;              // [P] workspace (update)
+  const uint32_t *sorted_row, *sorted_part;  // rows in partition order (update, may be null)
   int64_t offset;            // first picked row, in [0, n) (init)
   int only_left;             // assign only the rows marked -1
   const uint64_t *packed;    // ... after unpacking (score, id) keys [n], may be null

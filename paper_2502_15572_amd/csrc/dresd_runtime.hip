@@ -726,6 +726,8 @@ dresd_status device_buffer(DeviceBuffers &db, int dev, size_t need, hipStream_t 
   return DRESD_OK;
 }
 
+// Least n d of a k-means update over sorted rows.
+constexpr int64_t kSortedUpdateWork = (int64_t)1 << 24;
 // Least n P d (multiply-adds) of a k-means assignment for the 16-bit path: its
 // three launches cost as much as the fp32 kernel's one below it (2,000 x 64
 // rows, 64 centroids: 18.2 against 16.0 us; 20,000 x 128, 312: 23.5 against 43.6).
@@ -1939,10 +1941,43 @@ dresd_status dresd_kmeans_update(const void *x, int64_t n, int32_t d, int32_t dt
   static DeviceBuffers bufs;
   const size_t need = (size_t)P * d * 8 + (size_t)P * 4;
   void *wsp = nullptr;
-  dresd_status s = device_buffer(bufs, dev, need, static_cast<hipStream_t>(stream),
-                                 "k-means workspace", &wsp);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  dresd_status s = device_buffer(bufs, dev, need, st, "k-means workspace", &wsp);
   if (s != DRESD_OK) return s;
   KmeansParams p = {};
+  // Many elements: rows sorted by partition first, so that a partition's sum
+  // takes one atomic per run of rows (524,288 x 128 f16, 8,192
+  // partitions: 398 -> 139 us; half of the rows in one partition: 5.8 -> 0.30 ms).
+  // Fewer than about 2^24 elements cost more to sort than their atomics take
+  // (100,000 x 64: 77 against 61 us).  Without a workspace for the
+  // sort (memory, or a first call inside a capture), or with more rows than
+  // 256 MiB of it holds, in row order.
+  static DeviceBuffers sort_bufs;
+  GroupParams gp = {};
+  gp.n = n;
+  gp.nblk = ceil_div(n, kGroupTile);
+  const size_t seq = ((size_t)n * 4 + 255) / 256 * 256;
+  void *sp = nullptr;
+  if (n * (int64_t)d >= kSortedUpdateWork && n <= (int64_t)1 << 24 &&
+      device_buffer(sort_bufs, dev, 4 * seq + 8192 + (size_t)gp.nblk * 1024, st,
+                    "k-means sort workspace", &sp) == DRESD_OK) {
+    unsigned char *b = static_cast<unsigned char *>(sp);
+    for (int i = 0; i < 2; ++i) {
+      gp.key[i] = reinterpret_cast<uint32_t *>(b + (size_t)(2 * i) * seq);
+      gp.row[i] = reinterpret_cast<uint32_t *>(b + (size_t)(2 * i + 1) * seq);
+    }
+    gp.hist = reinterpret_cast<uint32_t *>(b + 4 * seq);
+    gp.bad = gp.hist + 1024;
+    gp.distinct = gp.hist + 1025;
+    gp.counts = reinterpret_cast<uint32_t *>(b + 4 * seq + 8192);
+    gp.assign = assign;
+    gp.P = P;
+    DRESD_HIP(launch_group_keys(gp, st));
+    for (int dg = 0; dg == 0 || (dg < 4 && (int64_t)P > (int64_t)1 << (8 * dg)); ++dg)
+      DRESD_HIP(launch_group_pass(gp, dg, dg == 0, st));
+    p.sorted_row = gp.row[gp.src];
+    p.sorted_part = gp.key[gp.src];
+  }
   p.x = x;
   p.n = n;
   p.d = d;
@@ -1953,7 +1988,7 @@ dresd_status dresd_kmeans_update(const void *x, int64_t n, int32_t d, int32_t dt
   p.counts = counts;
   p.sums = static_cast<long long *>(wsp);
   p.cnt = reinterpret_cast<int32_t *>(static_cast<unsigned char *>(wsp) + (size_t)P * d * 8);
-  DRESD_HIP(launch_kmeans_update(p, cus, static_cast<hipStream_t>(stream)));
+  DRESD_HIP(launch_kmeans_update(p, cus, st));
   return DRESD_OK;
 }
 
