@@ -397,7 +397,7 @@ int spec_rank(int k, int64_t r) {
 }
 
 dresd_status make_plan(dresd_index *ix, int B, int k, Plan &pl, bool filt = false,
-                       bool keep_cache = true, bool tc32 = true) {
+                       bool keep_cache = true, bool tc32 = true, bool small_ok = true) {
   pl = Plan();
   pl.filt = filt;
   // The query enters the matrix cores as three 16-bit parts that sum to it
@@ -478,7 +478,7 @@ dresd_status make_plan(dresd_index *ix, int B, int k, Plan &pl, bool filt = fals
   // query few candidates, past 32 MiB (262,144 x 128 f16 28.2 against 27.5).
   // Waves of 16 blocks or fewer take several tiles while that leaves more
   // lists than CUs.
-  if (!pl.tc && !(mq_type && mq_kb && (qt_all >= 2 || pl.terms < 4)) &&
+  if (small_ok && !pl.tc && !(mq_type && mq_kb && (qt_all >= 2 || pl.terms < 4)) &&
       (ix->dtype == kF32 || pl.terms == 4) && ix->KB <= 32 && ix->T <= 4 * kMergeLists &&
       ix->T * ix->KB <= (filt && B == 1 ? kSmallBlocks / 4 : kSmallBlocks) &&
       (int64_t)B * ix->T <= kSmallTiles) {
@@ -1043,6 +1043,11 @@ dresd_status search_impl(dresd_index *ix, const float *queries, const int32_t *n
   // 64 queries).
   if (fixed && pl.bytes > fixed_bytes && pl.tc && ix->KB == 32) {
     s = make_plan(ix, B, k, pl, next_tok != nullptr, false, false);
+    if (s != DRESD_OK) return s;
+  }
+  // Nor for lists of whole tiles: the single-tile scan's are shorter.
+  if (fixed && pl.bytes > fixed_bytes && pl.small) {
+    s = make_plan(ix, B, k, pl, next_tok != nullptr, false, true, false);
     if (s != DRESD_OK) return s;
   }
   unsigned char *ws = fixed_ws;

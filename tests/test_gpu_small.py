@@ -141,3 +141,25 @@ def test_few_and_many_tiles(gpu_lib, k):
                 lambda b, rows: oracle.score_rows(kb, dt, q[b], rows), N, cont, 1e-5,
                 admitted_b=lambda b, rows: np.isin(a[rows], list(sets[b])))
     ix.close()
+
+
+@pytest.mark.parametrize("B", [4, 16])
+def test_small_search_without_allocation(gpu_lib, B):
+    """The allocation-free search takes whole-tile lists where they fit its
+    scratch (B = 4) and the single-tile scan's shorter ones where they do not."""
+    from paper_2502_15572_amd import Index
+    from test_zz_no_alloc import _noalloc, _outs
+    say("small search without allocation", B)
+    N, d, k = 262144, 32, 10
+    keys, q, cont, _ = data("f32", N, d, B, 9)
+    ix = Index(keys.to(DEV), torch.from_numpy(cont).to(DEV))
+    q = q.to(DEV)
+    assert (ix.plan(B, k)["workspace_bytes"] <= 64 << 20) == (B == 4)
+    ref = ix.search(q, k)
+    out = _outs(B, k, cont.shape[1])
+    assert _noalloc(gpu_lib, ix, q, out) == 0, gpu_lib.dresd_last_error()
+    torch.cuda.synchronize()
+    # fp32 sums of the same products in the same order
+    for a, b in zip(out, ref):
+        assert torch.equal(a, b)
+    ix.close()
