@@ -264,7 +264,8 @@ dresd_status dresd_bw_probe(const void *buf, int64_t bytes, int32_t reps, int32_
  * use a library buffer per (device, stream) that is allocated (synchronously)
  * on the first call on that stream that needs a larger one and kept, like
  * every buffer it outgrows, until the process ends: calls on different
- * streams may overlap, calls on one stream are ordered by it.
+ * streams may overlap, calls on one stream are ordered by it, also when several
+ * host threads make them.
  * Errors: EINVAL (null pointer with M > 0, sizes or eps out of range),
  * ENOMEM, EUNSUPPORTED (the buffer would have to grow during stream
  * capture), EDEVICE.
@@ -428,7 +429,8 @@ dresd_status dresd_ivf_search_next_token(dresd_ivf *ivf, const float *queries,
  *   2^24 elements to 2^24 rows, where it can be had, 16 n more to sort them) per
  *   (device, stream), allocated (synchronously) on first use on that stream
  *   and kept, like every buffer it outgrows, until the process ends: calls
- *   on different streams may overlap, calls on one stream are ordered by it.
+ *   on different streams may overlap, calls on one stream are ordered by it,
+ *   also when several host threads make them.
  * dresd_kmeans_init: the starting centroids of the iteration: P distinct
  *   rows spread evenly through the row order, centroid j = row pick(j)
  *   scaled to unit length (a zero row gives a zero centroid), with

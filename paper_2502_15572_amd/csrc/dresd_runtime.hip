@@ -695,21 +695,35 @@ dresd_status ensure_workspace(dresd_index *ix, size_t bytes, hipStream_t st,
 
 // Library buffers kept until the process ends (the transform's partial
 // sums, the k-means sums), one per (device, stream): calls on different
-// streams never share one, and calls on one stream are ordered by it.  One
-// grows (allocating synchronously) when a call needs more; the buffer it
-// outgrows is kept as well, because a graph captured from an earlier call
-// may still replay on it.
+// streams never share one, and calls on one stream are ordered by it.  A
+// call's kernels only find in the buffer what the call's own earlier kernels
+// wrote if no other call's kernels come between them on the stream: a call
+// holds its buffer's lock until its last kernel is launched, so host threads
+// that share a stream (torch's default stream is one for all threads) take
+// turns.  A buffer grows (allocating synchronously) when a call needs more;
+// the one it outgrows is kept as well, because a graph captured from an
+// earlier call may still replay on it.
 struct DeviceBuffers {
-  std::mutex mu;
-  std::map<std::pair<int, hipStream_t>, std::pair<void *, size_t>> cur;
+  struct Buffer {
+    std::mutex use;
+    void *ptr = nullptr;
+    size_t bytes = 0;
+  };
+  std::mutex mu;  // of the map and of retired
+  std::map<std::pair<int, hipStream_t>, Buffer> cur;
   std::vector<void *> retired;
 };
 
+// The buffer for (dev, st), at least `need` bytes, with its lock in `use`.
 dresd_status device_buffer(DeviceBuffers &db, int dev, size_t need, hipStream_t st,
-                           const char *what, void **out) {
-  std::lock_guard<std::mutex> lock(db.mu);
-  auto &c = db.cur[{dev, st}];
-  if (c.second < need) {
+                           const char *what, void **out, std::unique_lock<std::mutex> &use) try {
+  DeviceBuffers::Buffer *c = nullptr;
+  {
+    std::lock_guard<std::mutex> lock(db.mu);
+    c = &db.cur[{dev, st}];  // (a map's elements stay where they are)
+  }
+  use = std::unique_lock<std::mutex>(c->use);
+  if (c->bytes < need) {
     if (capturing(st))
       return fail(DRESD_EUNSUPPORTED, std::string(what) +
                                           " must grow while the stream is being captured; run one "
@@ -719,11 +733,18 @@ dresd_status device_buffer(DeviceBuffers &db, int dev, size_t need, hipStream_t 
       (void)hipGetLastError();
       return fail(DRESD_ENOMEM, std::string(what) + " allocation failed");
     }
-    if (c.first) db.retired.push_back(c.first);
-    c = {b, need};
+    void *old = c->ptr;
+    c->ptr = b;
+    c->bytes = need;
+    if (old) {
+      std::lock_guard<std::mutex> lock(db.mu);
+      db.retired.push_back(old);
+    }
   }
-  *out = c.first;
+  *out = c->ptr;
   return DRESD_OK;
+} catch (const std::bad_alloc &) {  // the host's own lists
+  return DRESD_ENOMEM;
 }
 
 // Least n d of a k-means update over sorted rows.
@@ -1249,13 +1270,15 @@ dresd_status dresd_transform(const float *x, int64_t M, int32_t D, const float *
   int cus = 0;
   DRESD_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   static DeviceBuffers bufs;
+  std::unique_lock<std::mutex> use;  // of the call's buffer, until its launches are made
   hipStream_t st = static_cast<hipStream_t>(stream);
   // Large batches on the 16-bit matrix cores; without a workspace for their
   // weight operands (memory, or a first call inside a capture) in fp32.
   ProjectParams pp;
   if (project_split_plan(M, D, l, cus, &pp)) {
     void *b = nullptr;
-    if (device_buffer(bufs, dev, (size_t)pp.bytes, st, "transform workspace", &b) == DRESD_OK) {
+    if (device_buffer(bufs, dev, (size_t)pp.bytes, st, "transform workspace", &b, use) ==
+        DRESD_OK) {
       pp.t.x = x;
       pp.t.mean = mean;
       pp.t.var = var;
@@ -1269,6 +1292,7 @@ dresd_status dresd_transform(const float *x, int64_t M, int32_t D, const float *
       DRESD_HIP(launch_project_split(pp, b, st));
       return DRESD_OK;
     }
+    use = {};
   }
   TransformParams p;
   p.splits = transform_splits(M, D, l, cus);
@@ -1279,7 +1303,7 @@ dresd_status dresd_transform(const float *x, int64_t M, int32_t D, const float *
     // the process).
     const size_t need = (size_t)p.splits * (size_t)M * (size_t)l * sizeof(float);
     void *b = nullptr;
-    dresd_status s = device_buffer(bufs, dev, need, st, "transform workspace", &b);
+    dresd_status s = device_buffer(bufs, dev, need, st, "transform workspace", &b, use);
     if (s != DRESD_OK) return s;
     p.part = static_cast<float *>(b);
   }
@@ -1913,8 +1937,9 @@ dresd_status dresd_kmeans_assign(const void *x, int64_t n, int32_t d, int32_t dt
   AssignParams ap;
   if (n * (int64_t)P * d >= kAssignSplitWork && assign_split_plan(n, d, dtype, P, cus, &ap)) {
     static DeviceBuffers bufs;
+    std::unique_lock<std::mutex> use;  // of the workspace, until the launches are made
     void *ws = nullptr;
-    if (device_buffer(bufs, dev, (size_t)ap.bytes, st, "k-means assignment workspace", &ws) ==
+    if (device_buffer(bufs, dev, (size_t)ap.bytes, st, "k-means assignment workspace", &ws, use) ==
         DRESD_OK) {
       ap.x = x;
       ap.centroids = centroids;
@@ -1947,7 +1972,9 @@ dresd_status dresd_kmeans_update(const void *x, int64_t n, int32_t d, int32_t dt
   const size_t need = (size_t)P * d * 8 + (size_t)P * 4;
   void *wsp = nullptr;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  dresd_status s = device_buffer(bufs, dev, need, st, "k-means workspace", &wsp);
+  // of the two buffers, always taken in this order, until the launches are made
+  std::unique_lock<std::mutex> use, sort_use;
+  dresd_status s = device_buffer(bufs, dev, need, st, "k-means workspace", &wsp, use);
   if (s != DRESD_OK) return s;
   KmeansParams p = {};
   // Many elements: rows sorted by partition first, so that a partition's sum
@@ -1965,7 +1992,7 @@ dresd_status dresd_kmeans_update(const void *x, int64_t n, int32_t d, int32_t dt
   void *sp = nullptr;
   if (n * (int64_t)d >= kSortedUpdateWork && n <= (int64_t)1 << 24 &&
       device_buffer(sort_bufs, dev, 4 * seq + 8192 + (size_t)gp.nblk * 1024, st,
-                    "k-means sort workspace", &sp) == DRESD_OK) {
+                    "k-means sort workspace", &sp, sort_use) == DRESD_OK) {
     unsigned char *b = static_cast<unsigned char *>(sp);
     for (int i = 0; i < 2; ++i) {
       gp.key[i] = reinterpret_cast<uint32_t *>(b + (size_t)(2 * i) * seq);
