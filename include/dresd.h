@@ -257,7 +257,8 @@ dresd_status dresd_bw_probe(const void *buf, int64_t bytes, int32_t reps, int32_
  * Arithmetic: fp32, the projection on the fp32 matrix cores, or for large
  * batches (at least 512 rows and about 2^30 multiply-adds) on the 16-bit ones
  * with z and W in three bf16 parts each that sum to them (error no larger; a
- * workspace of 6 D l bytes, at most 256 MiB; without it in fp32); batches with
+ * workspace of 6 D l bytes, at most 256 MiB; in fp32 without it and inside a
+ * capture, whose graph may replay on any stream); batches with
  * few output tiles split D across workgroups and add the partial sums in a
  * fixed order, so results are deterministic.  Ownership: all buffers are
  * caller-owned and must stay alive until `stream` completes; the partial sums
@@ -265,7 +266,9 @@ dresd_status dresd_bw_probe(const void *buf, int64_t bytes, int32_t reps, int32_
  * on the first call on that stream that needs a larger one and kept, like
  * every buffer it outgrows, until the process ends: calls on different
  * streams may overlap, calls on one stream are ordered by it, also when several
- * host threads make them.
+ * host threads make them.  A graph captured from a call that splits D uses that
+ * stream's buffer: it must not replay beside calls on the stream, or beside
+ * another such graph.
  * Errors: EINVAL (null pointer with M > 0, sizes or eps out of range),
  * ENOMEM, EUNSUPPORTED (the buffer would have to grow during stream
  * capture), EDEVICE.
@@ -418,7 +421,8 @@ dresd_status dresd_ivf_search_next_token(dresd_ivf *ivf, const float *queries,
  *   256 dims are multiplied on the 16-bit matrix cores (the centroids split
  *   into three exact parts) with a workspace of about 6 P d bytes (at most
  *   256 MiB; 8 n more for small n) per (device, stream), kept as for
- *   dresd_kmeans_update; a call that cannot get one runs without.
+ *   dresd_kmeans_update; a call that cannot get one, or that is captured (its
+ *   graph may replay on any stream), runs in fp32 without.
  * dresd_kmeans_update: each centroid becomes the unit vector along the sum of
  *   the rows assigned to it; a centroid with no rows (or a zero sum) is left
  *   as it is.  Sums are exact to 2^-30 per element and independent of the
@@ -426,11 +430,14 @@ dresd_status dresd_ivf_search_next_token(dresd_ivf *ivf, const float *queries,
  *   device [n] int32, each in [0, P) (not checked: the caller's contract);
  *   centroids device [P, d] fp32 in/out; counts device [P] int32 out (rows per
  *   centroid, NULL allowed).  Uses a workspace of P*d*8 + P*4 bytes (and, from
- *   2^24 elements to 2^24 rows, where it can be had, 16 n more to sort them) per
+ *   2^24 elements to 2^24 rows, where it can be had and outside captures, 16 n
+ *   more to sort them) per
  *   (device, stream), allocated (synchronously) on first use on that stream
  *   and kept, like every buffer it outgrows, until the process ends: calls
  *   on different streams may overlap, calls on one stream are ordered by it,
- *   also when several host threads make them.
+ *   also when several host threads make them.  A graph captured from an
+ *   update uses that stream's buffer of sums: it must not replay beside
+ *   updates on the stream, or beside another such graph.
  * dresd_kmeans_init: the starting centroids of the iteration: P distinct
  *   rows spread evenly through the row order, centroid j = row pick(j)
  *   scaled to unit length (a zero row gives a zero centroid), with

@@ -747,6 +747,12 @@ dresd_status device_buffer(DeviceBuffers &db, int dev, size_t need, hipStream_t 
   return DRESD_ENOMEM;
 }
 
+// Whether a call that can do without a workspace may use its stream's: not
+// inside a capture, whose graph may replay on any stream, beside other graphs
+// and calls of this one, and not on the per-thread default stream, whose
+// handle names another stream in each thread.
+bool may_use_buffer(hipStream_t st) { return st != hipStreamPerThread && !capturing(st); }
+
 // Least n d of a k-means update over sorted rows.
 constexpr int64_t kSortedUpdateWork = (int64_t)1 << 24;
 // Least n P d (multiply-adds) of a k-means assignment for the 16-bit path: its
@@ -1269,15 +1275,21 @@ dresd_status dresd_transform(const float *x, int64_t M, int32_t D, const float *
   DRESD_HIP(hipGetDevice(&dev));
   int cus = 0;
   DRESD_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-  static DeviceBuffers bufs;
-  std::unique_lock<std::mutex> use;  // of the call's buffer, until its launches are made
+  static DeviceBuffers bufs, split_bufs;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  TransformParams p;
+  p.splits = transform_splits(M, D, l, cus);
+  const size_t need = (size_t)p.splits * (size_t)M * (size_t)l * sizeof(float);
   // Large batches on the 16-bit matrix cores; without a workspace for their
-  // weight operands (memory, or a first call inside a capture) in fp32.
+  // weight operands (no memory, or inside a capture) in fp32.
   ProjectParams pp;
-  if (project_split_plan(M, D, l, cus, &pp)) {
+  if (may_use_buffer(st) && project_split_plan(M, D, l, cus, &pp)) {
+    std::unique_lock<std::mutex> use;  // of the workspace, until the launches are made
     void *b = nullptr;
-    if (device_buffer(bufs, dev, (size_t)pp.bytes, st, "transform workspace", &b, use) ==
+    // A later capture of this shape runs in fp32 and cannot allocate.
+    if (p.splits > 1) (void)device_buffer(bufs, dev, need, st, "transform workspace", &b, use);
+    use = {};
+    if (device_buffer(split_bufs, dev, (size_t)pp.bytes, st, "transform workspace", &b, use) ==
         DRESD_OK) {
       pp.t.x = x;
       pp.t.mean = mean;
@@ -1292,16 +1304,13 @@ dresd_status dresd_transform(const float *x, int64_t M, int32_t D, const float *
       DRESD_HIP(launch_project_split(pp, b, st));
       return DRESD_OK;
     }
-    use = {};
   }
-  TransformParams p;
-  p.splits = transform_splits(M, D, l, cus);
   p.dslice = (int)ceil_div(D, p.splits);
   p.part = nullptr;
+  std::unique_lock<std::mutex> use;
   if (p.splits > 1) {
     // Partial sums of the D slices (a per-device buffer kept for the life of
     // the process).
-    const size_t need = (size_t)p.splits * (size_t)M * (size_t)l * sizeof(float);
     void *b = nullptr;
     dresd_status s = device_buffer(bufs, dev, need, st, "transform workspace", &b, use);
     if (s != DRESD_OK) return s;
@@ -1933,9 +1942,10 @@ dresd_status dresd_kmeans_assign(const void *x, int64_t n, int32_t d, int32_t dt
   DRESD_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   // On the 16-bit matrix cores where the rows are narrow enough and the
   // centroid operands have a workspace; the fp32 kernel needs none, so a call
-  // that cannot get one (memory, or a first call inside a capture) runs there.
+  // that cannot use one (no memory, or inside a capture) runs there.
   AssignParams ap;
-  if (n * (int64_t)P * d >= kAssignSplitWork && assign_split_plan(n, d, dtype, P, cus, &ap)) {
+  if (n * (int64_t)P * d >= kAssignSplitWork && may_use_buffer(st) &&
+      assign_split_plan(n, d, dtype, P, cus, &ap)) {
     static DeviceBuffers bufs;
     std::unique_lock<std::mutex> use;  // of the workspace, until the launches are made
     void *ws = nullptr;
@@ -1982,15 +1992,15 @@ dresd_status dresd_kmeans_update(const void *x, int64_t n, int32_t d, int32_t dt
   // partitions: 398 -> 139 us; half of the rows in one partition: 5.8 -> 0.30 ms).
   // Fewer than about 2^24 elements cost more to sort than their atomics take
   // (100,000 x 64: 77 against 61 us).  Without a workspace for the
-  // sort (memory, or a first call inside a capture), or with more rows than
-  // 256 MiB of it holds, in row order.
+  // sort (no memory, or inside a capture), or with more rows than 256 MiB of
+  // it holds, in row order.
   static DeviceBuffers sort_bufs;
   GroupParams gp = {};
   gp.n = n;
   gp.nblk = ceil_div(n, kGroupTile);
   const size_t seq = ((size_t)n * 4 + 255) / 256 * 256;
   void *sp = nullptr;
-  if (n * (int64_t)d >= kSortedUpdateWork && n <= (int64_t)1 << 24 &&
+  if (n * (int64_t)d >= kSortedUpdateWork && n <= (int64_t)1 << 24 && may_use_buffer(st) &&
       device_buffer(sort_bufs, dev, 4 * seq + 8192 + (size_t)gp.nblk * 1024, st,
                     "k-means sort workspace", &sp, sort_use) == DRESD_OK) {
     unsigned char *b = static_cast<unsigned char *>(sp);
