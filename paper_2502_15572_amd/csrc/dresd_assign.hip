@@ -192,6 +192,7 @@ __global__ void __launch_bounds__(256, 2) dresd_assign_split(AssignParams p) {
 
   // Rows: lane (g, m) holds dims 8 g .. + 8 of every block of row m of every tile.
   u4 x[RT][KB * XP];
+  uint32_t tiny = 0;  // fp32 rows: bit r, row m of tile r is nonzero and below 2^-100
   {
     const int es = DT == kF32 ? 4 : 2;
     const bool vec = (((uintptr_t)p.x & 15u) == 0) && ((int64_t)d * es) % 16 == 0;
@@ -199,6 +200,7 @@ __global__ void __launch_bounds__(256, 2) dresd_assign_split(AssignParams p) {
     for (int r = 0; r < RT; ++r) {
       const int64_t row = r0 + r * 16 + m;
       const bool in = row < p.n;
+      float big = 0.f;
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb) {
         const int k = kb * 32 + g * 8;
@@ -222,6 +224,7 @@ __global__ void __launch_bounds__(256, 2) dresd_assign_split(AssignParams p) {
             part[0][i] = a;
             part[1][i] = b;
             part[2][i] = c;
+            big = fmaxf(big, fabsf(v[i]));
           }
 #pragma unroll
           for (int q = 0; q < 3; ++q) x[r][kb * 3 + q] = __builtin_bit_cast(u4, part[q]);
@@ -236,6 +239,11 @@ __global__ void __launch_bounds__(256, 2) dresd_assign_split(AssignParams p) {
             x[r][kb] = __builtin_bit_cast(u4, v);
           }
         }
+      }
+      if constexpr (DT == kF32) {
+        big = fmaxf(big, __shfl_xor(big, 16, kWaveSize));
+        big = fmaxf(big, __shfl_xor(big, 32, kWaveSize));
+        if (big > 0.f && big < 0x1p-100f) tiny |= 1u << r;
       }
     }
   }
@@ -348,9 +356,10 @@ __global__ void __launch_bounds__(256, 2) dresd_assign_split(AssignParams p) {
       }
     }
     const int64_t row = r0 + r * 16 + m;
-    // fp32 rows of vanishing size lose their lower parts: left to fp32
+    // fp32 rows lose lower parts where their elements or scores vanish (bf16
+    // ends at 2^-133, a score of size 2^-80 has parts down to 2^-104): left to fp32
     const bool fine = id >= 0 && fabsf(b) < __builtin_inff() &&
-                      (DT != kF32 || b == 0.f || fabsf(b) >= 0x1p-80f);
+                      (DT != kF32 || (!((tiny >> r) & 1u) && (b == 0.f || fabsf(b) >= 0x1p-80f)));
     if (g == (r & 3) && row < p.n) {
       if (p.packed) {
         atomicMax(reinterpret_cast<unsigned long long *>(p.packed + row),

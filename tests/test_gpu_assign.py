@@ -150,6 +150,28 @@ def test_centroid_scales(gpu_lib, dt):
         assert np.all(S[np.arange(n), a.cpu().numpy()] >= ob - tol)
 
 
+@pytest.mark.parametrize("dt,ex,ec", [("f32", -95, 60), ("f32", -118, 70), ("f32", -122, 100),
+                                      ("f32", -130, 110), ("bf16", -130, 110),
+                                      ("f16", -18, 30)])
+def test_vanishing_rows_large_centroids(gpu_lib, dt, ex, ec):
+    """Rows so small that bf16 does not hold their lower parts, against
+    centroids that bring the scores back into range: no further from 64 bits
+    than an fp32 sum of the rows' own values."""
+    from paper_2502_15572_amd import kmeans_assign
+    n, d, P = 3000, 96, 200
+    say("vanishing rows, large centroids", dt, ex, ec)
+    rng = np.random.default_rng(13)
+    keys = as_keys(unit(rng, n, d) * 2.0 ** ex, dt)
+    c = (unit(rng, P, d) * 2.0 ** ec).astype(np.float32)
+    x = oracle.decode_keys(to_numpy_bits(keys)[0], dt)
+    a, sc = kmeans_assign(keys.to(DEV), torch.from_numpy(c).to(DEV), with_score=True)
+    torch.cuda.synchronize()
+    oa, ob, S = oracle.kmeans_assign(x.astype(np.float64), c.astype(np.float64))
+    tol = (d + 2) * 2.0 ** -24 * 2.0 ** (ex + ec)
+    assert np.all(np.abs(sc.cpu().numpy() - ob) <= tol)
+    assert np.all(S[np.arange(n), a.cpu().numpy()] >= ob - tol)
+
+
 def test_assign_on_two_streams(gpu_lib):
     """Assignments on two streams, each with its own workspace, equal the
     ones computed alone."""
