@@ -43,6 +43,8 @@ struct TransformParams {
 // Splits of D for an M x l output on a device with `cus` compute units.
 int transform_splits(int64_t M, int D, int l, int cus);
 hipError_t launch_transform(const TransformParams &p, hipStream_t st);
+// Its second kernel alone: adds the partial sums (splits > 1), unit rows.
+hipError_t launch_finish_rows(const TransformParams &p, hipStream_t st);
 
 // Datastore-sized batches on the 16-bit matrix cores (dresd_project.hip).
 struct ProjectParams {

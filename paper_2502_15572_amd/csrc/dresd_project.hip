@@ -24,8 +24,12 @@
 // rows -> 1,024 in 0.48 ms (0.81 ms).  Back to back the clock falls under the
 // matrix load (0.34 ms for a launch on its own).
 //
-// Rows whose sum of squares is not finite or vanishes (a value outside the
-// split's range, or a result that is itself so) are computed again in fp32.
+// What the split does not hold (values that are not finite or past bf16's
+// rounding range, rows so small that lower parts are lost) shows in a row's sum of squares: the workgroup that
+// holds the row computes it again on the fp32 matrix cores, for its columns
+// and its slice of D.  65,536 x 4,096 -> 128 with 65 / 6,553 / all rows in
+// doubt: 0.53 / 0.78 / 1.96 ms (the whole batch in fp32 0.93 ms; each wave one
+// of its rows after another 3.4 / 21 / 65 ms).
 #include "dresd_device.h"
 #include "dresd_ops.h"
 
@@ -109,22 +113,6 @@ __device__ __forceinline__ void copy4_nt_to_lds(const void *base, uint32_t off, 
       :
       : "v"(off), "s"(base), "s"(lds)
       : "memory");
-}
-
-// Column c of `row` in fp32 (the values the split does not hold).
-__device__ __forceinline__ float exact_column(const TransformParams &t, int64_t row, int c) {
-  float v = 0.f;
-  for (int k = 0; k < t.D; ++k) {
-    const float z = (t.x[row * t.D + k] - t.mean[k]) * (1.0f / sqrtf(t.var[k] + t.eps_z));
-    v = fmaf(z, t.W[(int64_t)k * t.l + c], v);
-  }
-  return v;
-}
-
-// A sum of squares that the split may have got wrong: not finite, or so
-// small that lower parts were lost (an exact zero row sums to 0).
-__device__ __forceinline__ bool doubtful(float ss, bool nonzero) {
-  return !(ss < __builtin_inff()) || (nonzero && ss < 0x1p-120f);
 }
 
 // WHOLE: the workgroup holds whole rows (one column group, D not split) and
@@ -297,114 +285,175 @@ __global__ void __launch_bounds__(64 * kPWaves, 2) dresd_project_split(ProjectPa
   }
   wait_vmcnt<0>();  // no LDS copy may land after the workgroup ends
 
+  // Sums of squares of this wave's rows: a row's columns lie in the 16 lanes of
+  // a group (columns past l are zero).
   const int l = p.t.l, c0 = gr * NT * 16;
-  if constexpr (!WHOLE) {
-    float *out = p.t.splits > 1 ? p.t.part + (size_t)blockIdx.z * p.t.M * l : p.t.y;
+  float ss[2][4];
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+  for (int h = 0; h < 2; ++h) {
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
+    for (int t = 0; t < NT; ++t) hi[h][t] += lo[h][t];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float s = 0.f;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) s += hi[h][t][i] * hi[h][t][i];
+#pragma unroll
+      for (int o = 1; o < 16; o <<= 1) s += __shfl_xor(s, o, kWaveSize);
+      ss[h][i] = s;
+    }
+  }
+  // Rows in doubt: not finite, or so small that lower parts were lost.  A row of
+  // zero z-scores is none.
+  const float low = 0x1p-60f;
+  const int kbeg = kb0 * 32, kend = kb1 * 32 < D ? kb1 * 32 : D;
+  uint32_t again = 0;  // bit 4 h + i: row 16 h + 4 g + i is in doubt
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool bad = !(ss[h][i] < __builtin_inff()) || sqrtf(ss[h][i]) < low;
+      if (bad && r0 + 16 * h + 4 * g + i < p.t.M) again |= 1u << (4 * h + i);
+    }
+  if (__ballot(again != 0)) {
+    for (int r = 0; r < 32; ++r) {
+      const int bit = 4 * (r >> 4) + (r & 3), of = (r >> 2) & 3;
+      if (!((__builtin_amdgcn_readlane(again, of * 16) >> bit) & 1u)) continue;
+      const float *row = p.t.x + (r0 + r) * D;
+      bool nz = false;
+      for (int k = kbeg + lane; k < kend && !nz; k += kWaveSize) {
+        const float *nm = p.norm + (k >> 5) * 64 + (k & 31);
+        nz = !((row[k] - nm[0]) * nm[32] == 0.f);
+      }
+      if (!__ballot(nz) && g == of) again &= ~(1u << bit);
+    }
+  }
+
+  // Sums; WHOLE: unit rows (Eq. 2).
+  float *out = p.t.splits > 1 ? p.t.part + (size_t)blockIdx.z * p.t.M * l : p.t.y;
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t row = r0 + 16 * h + 4 * g + i;
+      const bool write = row < p.t.M && !((again >> (4 * h + i)) & 1u);
+      const float inv = WHOLE ? 1.0f / fmaxf(sqrtf(ss[h][i]), p.t.eps_n) : 1.f;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int c = c0 + t * 16 + m;
+        if (write && c < l) out[row * l + c] = WHOLE ? hi[h][t][i] * inv : hi[h][t][i];
+      }
+    }
+  if (!__syncthreads_or(again != 0)) return;
+
+  // The workgroup's rows in doubt, 32 at a time, one tile of columns per wave:
+  // list of the rows (any order: each has sums of its own), then their sums.
+  int32_t *list = reinterpret_cast<int32_t *>(smem), *nlist = list + kPRows;
+  float *sums = reinterpret_cast<float *>(smem) + 512;  // [32][NT * 16]
+  if (tid == 0) *nlist = 0;
+  __syncthreads();
+  if (m == 0)
+    for (uint32_t left = again; left; left &= left - 1) {
+      const int bit = __ffs((int)left) - 1;
+      list[atomicAdd(nlist, 1)] = wv * 32 + 16 * (bit >> 2) + 4 * g + (bit & 3);
+    }
+  __syncthreads();
+  const int total = *nlist;
+  for (int b0 = 0; b0 < total; b0 += 32) {
+    const float *xa[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int at = b0 + 16 * h + m < total ? b0 + 16 * h + m : total - 1;
+      xa[h] = p.t.x + ((int64_t)blockIdx.x * kPRows + list[at]) * D;
+    }
+    if (wv < NT) {
+      // Step e of a block of 32 dims multiplies dims 8 g + e, so that a lane's x
+      // and norms are eight in a row; four blocks' loads are in flight.
+      const int c = c0 + wv * 16 + m;
+      const float *wc = p.t.W + (c < l ? c : l - 1);
+      f4 acc[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
+      constexpr int U = 4;
+#pragma unroll 1
+      for (int kb = kb0; kb < kb1; kb += U) {
+        float xv[U][2][8], w[U][8];
+        float4 nm[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int k0 = (kb + u < kb1 ? kb + u : kb1 - 1) * 32 + g * 8;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            if constexpr (VEC) {
+#pragma unroll
+              for (int e = 0; e < 8; e += 4) {
+                const float4 v =
+                    *reinterpret_cast<const float4 *>(xa[h] + (k0 + e < D ? k0 + e : D - 4));
+                xv[u][h][e] = v.x, xv[u][h][e + 1] = v.y;
+                xv[u][h][e + 2] = v.z, xv[u][h][e + 3] = v.w;
+              }
+            } else {
+#pragma unroll
+              for (int e = 0; e < 8; ++e) xv[u][h][e] = xa[h][k0 + e < D ? k0 + e : D - 1];
+            }
+          }
+#pragma unroll
+          for (int e = 0; e < 8; ++e) w[u][e] = wc[(int64_t)(k0 + e < D ? k0 + e : D - 1) * l];
+          const float *n0 = p.norm + (k0 >> 5) * 64 + g * 8;
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            nm[u][e] = *reinterpret_cast<const float4 *>(n0 + (e & 1) * 4 + (e >> 1) * 32);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int k0 = (kb + u) * 32 + g * 8;
+          if (kb + u < kb1) {
+            const float mu[8] = {nm[u][0].x, nm[u][0].y, nm[u][0].z, nm[u][0].w,
+                                 nm[u][1].x, nm[u][1].y, nm[u][1].z, nm[u][1].w};
+            const float inv[8] = {nm[u][2].x, nm[u][2].y, nm[u][2].z, nm[u][2].w,
+                                  nm[u][3].x, nm[u][3].y, nm[u][3].z, nm[u][3].w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const bool in = k0 + e < D;
+              const float wv1 = in && c < l ? w[u][e] : 0.f;
+#pragma unroll
+              for (int h = 0; h < 2; ++h) {
+                const float z1 = in ? (xv[u][h][e] - mu[e]) * inv[e] : 0.f;
+                acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(z1, wv1, acc[h], 0, 0, 0);
+              }
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int64_t row = r0 + 16 * h + 4 * g + i;
-          const int c = c0 + t * 16 + m;
-          if (row < p.t.M && c < l) out[row * l + c] = hi[h][t][i] + lo[h][t][i];
+          const int r = 16 * h + 4 * g + i;
+          if constexpr (WHOLE) {
+            sums[r * (NT * 16) + wv * 16 + m] = acc[h][i];
+          } else if (b0 + r < total && c < l) {
+            out[((int64_t)blockIdx.x * kPRows + list[b0 + r]) * l + c] = acc[h][i];
+          }
         }
-  } else {
-    // Unit rows (Eq. 2): a row's columns lie in the 16 lanes of a group.
-    uint32_t again = 0;  // bit 4 h + i: row 16 h + 4 g + i is in doubt
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float ss = 0.f;
-        bool nz = false;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const float v = hi[h][t][i] + lo[h][t][i];
-          hi[h][t][i] = v;
-          ss += v * v;  // (columns past l are zero)
-          nz |= v != 0.f;
-        }
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) ss += __shfl_xor(ss, o, kWaveSize);
-        nz = (__ballot(nz) >> (16 * g)) & 0xFFFFull;
-        if (doubtful(ss, nz)) again |= 1u << (4 * h + i);
-        const float inv = 1.0f / fmaxf(sqrtf(ss), p.t.eps_n);
-        const int64_t row = r0 + 16 * h + 4 * g + i;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const int c = t * 16 + m;
-          if (row < p.t.M && c < l) p.t.y[row * l + c] = hi[h][t][i] * inv;
-        }
-      }
-    if (__ballot(again != 0)) {
-      for (int r = 0; r < 32; ++r) {
-        const uint32_t mine = __shfl(again, ((r >> 2) & 3) * 16, kWaveSize);
-        const int64_t row = r0 + r;
-        if (!((mine >> (4 * (r >> 4) + (r & 3))) & 1u) || row >= p.t.M) continue;
-        float v[2], ss = 0.f;  // l <= 128
+    }
+    if constexpr (WHOLE) {
+      __syncthreads();
+      for (int r = wv; r < 32 && b0 + r < total; r += kPWaves) {
+        float v[2], s = 0.f;  // NT * 16 <= 128 columns, zero past l
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-          const int c = lane + 64 * j;
-          v[j] = c < l ? exact_column(p.t, row, c) : 0.f;
-          ss += v[j] * v[j];
+          v[j] = lane + 64 * j < NT * 16 ? sums[r * (NT * 16) + lane + 64 * j] : 0.f;
+          s += v[j] * v[j];
         }
-        for (int o = 1; o < kWaveSize; o <<= 1) ss += __shfl_xor(ss, o, kWaveSize);
-        const float inv = 1.0f / fmaxf(sqrtf(ss), p.t.eps_n);
+        for (int o = 1; o < kWaveSize; o <<= 1) s += __shfl_xor(s, o, kWaveSize);
+        const float inv = 1.0f / fmaxf(sqrtf(s), p.t.eps_n);
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          if (lane + 64 * j < l) p.t.y[row * l + lane + 64 * j] = v[j] * inv;
+          if (lane + 64 * j < l)
+            out[((int64_t)blockIdx.x * kPRows + list[b0 + r]) * l + lane + 64 * j] = v[j] * inv;
       }
+      __syncthreads();
     }
   }
-}
-
-// One workgroup per row: partial sums in slice order, unit length (as
-// dresd_finish_rows), doubtful rows again in fp32.
-__global__ void __launch_bounds__(1024) dresd_project_finish(ProjectParams p) {
-  __shared__ float part_ss[16];
-  const TransformParams &t = p.t;
-  const int64_t row = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int nth = blockDim.x, nw = nth / kWaveSize;
-  const int64_t n = t.M * t.l;
-  float *y = t.y + row * t.l;
-  auto total = [&](float ss) {
-    for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, kWaveSize);
-    if (lane == 0) part_ss[wid] = ss;
-    __syncthreads();
-    float tot = 0.f;
-    for (int w = 0; w < nw; ++w) tot += part_ss[w];
-    return tot;
-  };
-  float ss = 0.f;
-  bool nz = false;
-  for (int c = tid; c < t.l; c += nth) {
-    float v;
-    if (t.splits > 1) {
-      v = 0.f;
-#pragma unroll 8
-      for (int s = 0; s < t.splits; ++s) v += t.part[(size_t)s * n + row * t.l + c];
-      y[c] = v;
-    } else {
-      v = y[c];
-    }
-    ss += v * v;
-    nz |= v != 0.f;
-  }
-  float tot = total(ss);
-  if (doubtful(tot, __syncthreads_or(nz))) {  // (the barrier also frees part_ss)
-    ss = 0.f;
-    for (int c = tid; c < t.l; c += nth) {
-      const float v = exact_column(t, row, c);
-      y[c] = v;
-      ss += v * v;
-    }
-    tot = total(ss);
-  }
-  const float inv = 1.0f / fmaxf(sqrtf(tot), t.eps_n);
-  for (int c = tid; c < t.l; c += nth) y[c] = y[c] * inv;
 }
 
 template <int NT>
@@ -489,10 +538,7 @@ hipError_t launch_project_split(ProjectParams &p, void *ws, hipStream_t st) {
     default: e = launch_nt<8>(p, st); break;
   }
   if (e != hipSuccess || (p.groups == 1 && p.t.splits == 1)) return e;
-  int nth = (p.t.l + kWaveSize - 1) / kWaveSize * kWaveSize;
-  nth = nth < 1024 ? nth : 1024;
-  return hipLaunchKernel((const void *)dresd_project_finish, dim3((unsigned)p.t.M),
-                         dim3((unsigned)nth), args, 0, st);
+  return launch_finish_rows(p.t, st);
 }
 
 }  // namespace dresd

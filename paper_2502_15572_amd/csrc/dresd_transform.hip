@@ -203,6 +203,12 @@ hipError_t launch_transform(const TransformParams &p, hipStream_t st) {
   const void *proj = wide ? (const void *)dresd_project<2, 64> : (const void *)dresd_project<1, 128>;
   hipError_t e = hipLaunchKernel(proj, grid1, dim3(256), args, 0, st);
   if (e != hipSuccess) return e;
+  return launch_finish_rows(p, st);
+}
+
+hipError_t launch_finish_rows(const TransformParams &p, hipStream_t st) {
+  TransformParams q = p;
+  void *args[] = {&q};
   const int fin = std::min(kFinishThreads, std::max(kWaveSize, (p.l + kWaveSize - 1) / kWaveSize * kWaveSize));
   return hipLaunchKernel((const void *)dresd_finish_rows, dim3((unsigned)p.M), dim3((unsigned)fin),
                          args, 0, st);

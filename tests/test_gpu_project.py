@@ -82,6 +82,39 @@ def test_rows_computed_again(gpu_lib, M, D, l):
     assert torch.equal(got[rest], ref[rest])
 
 
+@pytest.mark.parametrize("M,D,l", [(9000, 999, 64), (1030, 4096, 128), (5000, 1000, 200)],
+                         ids=["whole", "split", "groups"])
+def test_every_row_computed_again(gpu_lib, M, D, l):
+    """A value past bf16's rounding range in most rows: as the fp32 kernels
+    give them (a captured call), the clean rows as without them."""
+    from paper_2502_15572_amd import transform
+    print("every row computed again", M, D, l, flush=True)
+    x, mean, var, W = make_case(M, D, l, seed=17)
+    mean[:] = 0.0
+    var[:] = 1.0
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+    clean = t(x)
+    args = (t(mean), t(var), t(W))
+    ref = transform(clean, *args, eps_z=0.0)
+    keep = np.arange(M) % 7 == 3
+    x[~keep, 5] = 3.395e38
+    dirty = t(x)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        got = transform(dirty, *args, eps_z=0.0, stream=s)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        fp32 = transform(dirty, *args, eps_z=0.0, stream=s)
+    g.replay()
+    torch.cuda.synchronize()
+    got, fp32, ref = got.cpu().numpy(), fp32.cpu().numpy(), ref.cpu().numpy()
+    assert np.array_equal(got[keep], ref[keep])
+    fin = np.isfinite(fp32)
+    assert np.array_equal(np.isfinite(got[~keep]), fin[~keep])
+    assert np.all(np.abs(got - fp32)[~keep & fin.all(axis=1)] <= (D + 10) * 2.0 ** -22)
+
+
 def test_project_first_call_inside_capture(gpu_lib):
     """No workspace yet on a capturing stream: the fp32 kernels run."""
     from paper_2502_15572_amd import transform
