@@ -51,8 +51,9 @@ struct ProjectParams {
   TransformParams t;         // splits: slices of whole 32-dim blocks (dslice unused)
   void *op;                  // weight operands
   float *norm;               // [KB][64] means and factors of a block's dims
+  float *wmax;               // per workgroup of the operand kernel: the largest weight
   int KB, NT, groups;        // 32-dim blocks, column tiles per workgroup, column groups
-  int64_t off_norm, off_part, bytes;  // workspace
+  int64_t off_norm, off_wmax, off_part, bytes;  // workspace
 };
 // Whether a batch runs there, and its shape and workspace.
 bool project_split_plan(int64_t M, int D, int l, int cus, ProjectParams *out);

@@ -25,7 +25,8 @@
 // matrix load (0.34 ms for a launch on its own).
 //
 // What the split does not hold (values that are not finite or past bf16's
-// rounding range, rows so small that lower parts are lost) shows in a row's sum of squares: the workgroup that
+// rounding range, rows so small beside the weights that lower parts are lost,
+// weights of such sizes) shows in a row's sum of squares: the workgroup that
 // holds the row computes it again on the fp32 matrix cores, for its columns
 // and its slice of D.  65,536 x 4,096 -> 128 with 65 / 6,553 / all rows in
 // doubt: 0.53 / 0.78 / 1.96 ms (the whole batch in fp32 0.93 ms; each wave one
@@ -56,25 +57,34 @@ __device__ __forceinline__ void split3(float x, uint16_t &a, uint16_t &b, uint16
 // Weight operands [group][block of 32 dims][tile][part][64 lanes] x 16 bytes
 // (lane (g, m): column m of the tile, dims 8 g .. + 8; zero past D and l), and
 // per block of dims 32 means and 32 factors 1 / sqrt(var + eps_z) (Eq. 1;
-// zero past D).  One wave per (tile, block).
+// zero past D), and per workgroup the largest size of its weights (infinity
+// where one is not finite).  One wave per (tile, block).
 __global__ void __launch_bounds__(256) dresd_project_operand(ProjectParams p) {
+  __shared__ float top[4];
   const int lane = threadIdx.x & 63, g = lane >> 4, m = lane & 15;
-  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int tiles = p.groups * p.NT;
-  if (i >= (int64_t)tiles * p.KB) return;
+  const int64_t last = (int64_t)tiles * p.KB - 1, mine = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t i = mine < last ? mine : last;  // (waves past the end write the last one again)
   const int kb = (int)(i / tiles), tile = (int)(i - (int64_t)kb * tiles);
   const int c = tile * 16 + m;
   us8 part[3];
+  float big = 0.f;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int k = kb * 32 + g * 8 + e;
     const float x = (k < p.t.D && c < p.t.l) ? p.t.W[(int64_t)k * p.t.l + c] : 0.f;
+    big = fabsf(x) <= big ? big : x == x ? fabsf(x) : __builtin_inff();
     uint16_t a, b, l;
     split3(x, a, b, l);
     part[0][e] = a;
     part[1][e] = b;
     part[2][e] = l;
   }
+#pragma unroll
+  for (int o = 1; o < kWaveSize; o <<= 1) big = fmaxf(big, __shfl_xor(big, o, kWaveSize));
+  if (lane == 0) top[threadIdx.x >> 6] = big;
+  __syncthreads();
+  if (threadIdx.x == 0) p.wmax[blockIdx.x] = fmaxf(fmaxf(fmaxf(top[0], top[1]), top[2]), top[3]);
   const int gr = tile / p.NT, t = tile - gr * p.NT;
   us8 *dst = static_cast<us8 *>(p.op) +
              (((int64_t)gr * p.KB + kb) * p.NT + t) * 3 * 64 + lane;
@@ -236,6 +246,10 @@ __global__ void __launch_bounds__(64 * kPWaves, 2) dresd_project_split(ProjectPa
   issue_x(kb0 + 1, 1);
   issue_w(kb0, 0);
   issue_x(kb0 + 2, 2);
+  // the largest weight's size
+  float wtop = 0.f;
+  for (int i = lane; i < (p.groups * NT * p.KB + 3) / 4; i += kWaveSize)
+    wtop = fmaxf(wtop, p.wmax[i]);
   wait_vmcnt<2 * (XC + 1) + CPW>();
   u4 z[2][3];
   scores(0, z);
@@ -303,16 +317,21 @@ __global__ void __launch_bounds__(64 * kPWaves, 2) dresd_project_split(ProjectPa
       ss[h][i] = s;
     }
   }
-  // Rows in doubt: not finite, or so small that lower parts were lost.  A row of
-  // zero z-scores is none.
-  const float low = 0x1p-60f;
+  // Rows in doubt: not finite; or a norm below 2^-60 or below largest weight x
+  // D x 2^-100, which lets a row's largest z-score lie below 2^-100, where its
+  // parts end (bf16: 2^-133) less than 33 bits further down; or any row if
+  // that is so of the weights.  A row of zero z-scores is none.
+#pragma unroll
+  for (int o = 1; o < kWaveSize; o <<= 1) wtop = fmaxf(wtop, __shfl_xor(wtop, o, kWaveSize));
+  const bool odd = wtop > 0.f && !(wtop >= 0x1p-100f && wtop <= 0x1p100f);
+  const float low = wtop > 0.f ? fmaxf(0x1p-60f, wtop * (float)D * 0x1p-100f) : 0.f;
   const int kbeg = kb0 * 32, kend = kb1 * 32 < D ? kb1 * 32 : D;
   uint32_t again = 0;  // bit 4 h + i: row 16 h + 4 g + i is in doubt
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const bool bad = !(ss[h][i] < __builtin_inff()) || sqrtf(ss[h][i]) < low;
+      const bool bad = odd || !(ss[h][i] < __builtin_inff()) || sqrtf(ss[h][i]) < low;
       if (bad && r0 + 16 * h + 4 * g + i < p.t.M) again |= 1u << (4 * h + i);
     }
   if (__ballot(again != 0)) {
@@ -512,7 +531,8 @@ bool project_split_plan(int64_t M, int D, int l, int cus, ProjectParams *out) {
     }
   }
   p.off_norm = (op + 255) / 256 * 256;
-  p.off_part = p.off_norm + ((int64_t)p.KB * 256 + 255) / 256 * 256;
+  p.off_wmax = p.off_norm + (int64_t)p.KB * 256;
+  p.off_part = p.off_wmax + ((int64_t)p.groups * p.NT * p.KB * 4 + 255) / 256 * 256;
   p.bytes = p.off_part + (p.t.splits > 1 ? (int64_t)p.t.splits * M * l * 4 : 0);
   return true;
 }
@@ -521,6 +541,7 @@ hipError_t launch_project_split(ProjectParams &p, void *ws, hipStream_t st) {
   unsigned char *b = static_cast<unsigned char *>(ws);
   p.op = b;
   p.norm = reinterpret_cast<float *>(b + p.off_norm);
+  p.wmax = reinterpret_cast<float *>(b + p.off_wmax);
   p.t.part = reinterpret_cast<float *>(b + p.off_part);
   void *args[] = {&p};
   const int64_t waves = (int64_t)p.groups * p.NT * p.KB;

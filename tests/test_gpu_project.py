@@ -82,6 +82,36 @@ def test_rows_computed_again(gpu_lib, M, D, l):
     assert torch.equal(got[rest], ref[rest])
 
 
+@pytest.mark.parametrize("ez,ew", [(-95, 30), (-118, 65), (-118, 90), (-140, 120), (60, -105),
+                                   (75, -115)])
+@pytest.mark.parametrize("M,D,l", [(16500, 1024, 64), (1030, 4096, 128), (9001, 515, 250)],
+                         ids=["whole", "split", "groups"])
+def test_scales_the_split_does_not_hold(gpu_lib, M, D, l, ez, ew):
+    """z-scores or weights so small that bf16 does not hold their lower parts,
+    beside weights or z-scores that bring the sums back into range: within the
+    fp32 bound of 64 bits per element, and together within what the rounding of
+    D / 4 fp32 partial sums adds up to as a random walk (2^-24 sqrt(D / 4); with
+    bf16's loss 1e-6 to 1e-5).  A row of zeros stays one."""
+    say = "scales z 2^%d W 2^%d" % (ez, ew)
+    print(say, M, D, l, flush=True)
+    rng = np.random.default_rng(M + D)
+    x = (rng.standard_normal((M, D)) * 2.0 ** ez).astype(np.float32)
+    W = (rng.standard_normal((D, l)) * 2.0 ** ew).astype(np.float32)
+    x[M - 2] = 0.0
+    mean, var = np.zeros(D, np.float32), np.ones(D, np.float32)
+    got = run(x, mean, var, W, eps_z=0.0, eps_n=1e-30)
+    rows = np.r_[0:300, M - 300:M]
+    want = oracle.transform(x[rows], mean, var, W, 0.0, 1e-30)
+    err = np.abs(got[rows] - want)
+    tol = bound(x[rows], mean, var, W, 0.0, want)
+    if ez < -126:  # x itself holds so few bits that z W can cancel further than bound() says
+        tol = tol + 2.0 ** -20
+    assert np.all(err <= tol), (float(err.max()), float((err / tol).max()))
+    if ez >= -126:
+        assert np.linalg.norm(err) <= 2.0 ** -24 * np.sqrt(D / 4) * np.linalg.norm(want)
+    assert not got[M - 2].any()
+
+
 @pytest.mark.parametrize("M,D,l", [(9000, 999, 64), (1030, 4096, 128), (5000, 1000, 200)],
                          ids=["whole", "split", "groups"])
 def test_every_row_computed_again(gpu_lib, M, D, l):
