@@ -20,6 +20,8 @@
 //   init   : the starting centroids, P distinct rows taken at even spacing
 //            through the row order from a seeded offset, each scaled to unit
 //            length.
+#include <algorithm>
+
 #include "dresd_device.h"
 #include "dresd_ops.h"
 
@@ -30,6 +32,7 @@ namespace {
 constexpr int kKR = 64;    // rows per workgroup
 constexpr int kKC = 64;    // centroids per tile
 constexpr int kKK = 128;   // dims staged per step
+constexpr int kLeftChunk = 2048;  // most rows whose left-over ones a workgroup lists at once
 constexpr double kFixScale = 1073741824.0;  // 2^30
 
 template <int DT>
@@ -49,15 +52,15 @@ __device__ __forceinline__ bool beats(float s, int id, float bs, int bid) {
   return s > bs || (s == bs && id < bid);
 }
 
-// Rows [r0, r0 + 64) x dims [k0, k0 + 128) of x, decoded to fp32, into xs
-// (zero past n and d): thread t takes row t / 4, dims 32 (t % 4) .. + 32,
-// with 16-byte loads when the rows allow them (`vec`).
+// Dims [k0, k0 + 128) of the block's 64 rows, decoded to fp32, into xs (zero
+// past d and where there is no row): thread t takes the block's row t / 4, which
+// is row `row` of x (n: none), dims 32 (t % 4) .. + 32, with 16-byte loads when
+// the rows allow them (`vec`).
 template <int DT>
-__device__ __forceinline__ void stage_rows(const KmeansParams &p, int64_t r0, int k0,
+__device__ __forceinline__ void stage_rows(const KmeansParams &p, int64_t row, int k0,
                                            float (*xs)[kKK + 1], bool vec) {
   const int tid = threadIdx.x;
   const int r = tid >> 2, kk = (tid & 3) * 32;
-  const int64_t row = r0 + r;
   const int d = p.d;
   if (vec && row < p.n && k0 + kk + 32 <= d) {
     if constexpr (DT == kF32) {
@@ -100,7 +103,7 @@ __device__ __forceinline__ void stage_rows(const KmeansParams &p, int64_t r0, in
   }
 }
 
-template <int DT>
+template <int DT, bool LEFT>
 __global__ void __launch_bounds__(256) dresd_kmeans_assign(KmeansParams p) {
   __shared__ float xs[kKR][kKK + 1];  // rows (padded: no bank conflicts)
   __shared__ float cs[kKK][kKC];      // centroids, dim-major
@@ -111,131 +114,156 @@ __global__ void __launch_bounds__(256) dresd_kmeans_assign(KmeansParams p) {
   const int es = DT == kF32 ? 4 : 2;
   const bool xvec = (((uintptr_t)p.x & 15u) == 0) && ((d * es) % 16 == 0);
   const bool cvec = (((uintptr_t)p.centroids & 15u) == 0) && (d % 4 == 0);
-  const int64_t nblk = (p.n + kKR - 1) / kKR;
-  for (int64_t rb = blockIdx.x; rb < nblk; rb += gridDim.x) {
-  const int64_t r0 = rb * kKR;
-  if (p.only_left) {
-    // rows the 16-bit path has done (unpacking its results); the rest stay
-    bool left = false;
-    if (tid < kKR && r0 + tid < p.n) {
-      const int64_t row = r0 + tid;
-      if (p.packed) {
-        const uint64_t key = p.packed[row];
-        left = key == ~0ull;
-        p.assign[row] = left ? -1 : (int32_t)~(uint32_t)key;
-        if (p.score && !left) p.score[row] = order_value((uint32_t)(key >> 32));
-      } else {
-        left = p.assign[row] == -1;
-      }
-    }
-    if (!__syncthreads_or(left)) continue;
-  }
-  // running best of rows wv*16 + 4g + i (identical in the 16 lanes of a group)
-  float best[4];
-  int bid[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    best[i] = -__builtin_inff();
-    bid[i] = 0x7fffffff;
-  }
-  // Centroid tile (c0, k0) goes through registers: thread t loads centroid
-  // c0 + t / 4, dims k0 + 32 (t % 4) .. + 32 (one tile ahead of its use).
-  float4 creg[8];
-  auto load_c = [&](int c0, int k0) {
-    const int c = c0 + (tid >> 2), kk = k0 + (tid & 3) * 32;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int k = kk + 4 * e;
-      const float *src = p.centroids + (int64_t)c * d + k;
-      if (c < P && cvec && k + 4 <= d) {
-        creg[e] = *reinterpret_cast<const float4 *>(src);
-      } else {
-        creg[e].x = (c < P && k < d) ? src[0] : 0.f;
-        creg[e].y = (c < P && k + 1 < d) ? src[1] : 0.f;
-        creg[e].z = (c < P && k + 2 < d) ? src[2] : 0.f;
-        creg[e].w = (c < P && k + 3 < d) ? src[3] : 0.f;
-      }
-    }
-  };
-  auto store_c = [&]() {
-    const int cl = tid >> 2, kk = (tid & 3) * 32;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      cs[kk + 4 * e][cl] = creg[e].x;
-      cs[kk + 4 * e + 1][cl] = creg[e].y;
-      cs[kk + 4 * e + 2][cl] = creg[e].z;
-      cs[kk + 4 * e + 3][cl] = creg[e].w;
-    }
-  };
-  // Rows of at most 128 dims are staged once for all centroid tiles.
-  const bool x_once = d <= kKK;
-  if (x_once) stage_rows<DT>(p, r0, 0, xs, xvec);
-  load_c(0, 0);
-  for (int c0 = 0; c0 < P; c0 += kKC) {
-    f4 acc[kKC / 16];
-#pragma unroll
-    for (int t = 0; t < kKC / 16; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < d; k0 += kKK) {
-      if (!x_once) stage_rows<DT>(p, r0, k0, xs, xvec);
-      store_c();
+  // The rows of a block: consecutive ones (one block per workgroup), or, of the
+  // rows left over by the 16-bit path, 64 at a time from the list that the
+  // workgroup makes of each chunk of rows (any order: no row's result depends
+  // on the others).  p.n stands for none.  524,288 x 128 f16 rows against 8,192
+  // centroids, of which 524 / 5,242 / 52,428 are left over: 3.3 / 3.3 / 4.9 ms; with
+  // every block of 64 rows that holds one computed whole 6.8 / 14.5 / 17.6, and
+  // all of them in fp32 15.2.
+  __shared__ uint16_t list[LEFT ? kLeftChunk : 1];
+  __shared__ int nlist;
+  int64_t c0row = (int64_t)blockIdx.x * (LEFT ? p.chunk : kKR);
+  do {
+    int blocks = 1, total = 0;
+    if constexpr (LEFT) {
+      if (tid == 0) nlist = 0;
       __syncthreads();
-      // the next centroid tile's loads overlap this tile's matrix work
-      int nk0 = k0 + kKK, nc0 = c0;
-      if (nk0 >= d) {
-        nk0 = 0;
-        nc0 = c0 + kKC;
+      for (int j = tid; j < p.chunk && c0row + j < p.n; j += 256) {
+        const int64_t row = c0row + j;
+        bool left;
+        if (p.packed) {
+          const uint64_t key = p.packed[row];
+          left = key == ~0ull;
+          if (!left) {
+            p.assign[row] = (int32_t)~(uint32_t)key;
+            if (p.score) p.score[row] = order_value((uint32_t)(key >> 32));
+          }
+        } else {
+          left = p.assign[row] == -1;
+        }
+        if (left) list[atomicAdd(&nlist, 1)] = (uint16_t)j;
       }
-      if (nc0 < P) load_c(nc0, nk0);
-      // lane (g, m) feeds A[row m][k g] and B[k g][centroid m]
+      __syncthreads();
+      total = nlist;
+      blocks = (total + kKR - 1) / kKR;
+    }
+    for (int blk = 0; blk < blocks; ++blk) {
+      auto row_of = [&](int j) -> int64_t {
+        if constexpr (!LEFT) return c0row + j;
+        return blk * kKR + j < total ? c0row + list[blk * kKR + j] : p.n;
+      };
+      const int64_t srow = row_of(tid >> 2);  // the row this thread stages
+      // running best of rows wv*16 + 4g + i (identical in the 16 lanes of a group)
+      float best[4];
+      int bid[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        best[i] = -__builtin_inff();
+        bid[i] = 0x7fffffff;
+      }
+      // Centroid tile (c0, k0) goes through registers: thread t loads centroid
+      // c0 + t / 4, dims k0 + 32 (t % 4) .. + 32 (one tile ahead of its use).
+      float4 creg[8];
+      auto load_c = [&](int c0, int k0) {
+        const int c = c0 + (tid >> 2), kk = k0 + (tid & 3) * 32;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int k = kk + 4 * e;
+          const float *src = p.centroids + (int64_t)c * d + k;
+          if (c < P && cvec && k + 4 <= d) {
+            creg[e] = *reinterpret_cast<const float4 *>(src);
+          } else {
+            creg[e].x = (c < P && k < d) ? src[0] : 0.f;
+            creg[e].y = (c < P && k + 1 < d) ? src[1] : 0.f;
+            creg[e].z = (c < P && k + 2 < d) ? src[2] : 0.f;
+            creg[e].w = (c < P && k + 3 < d) ? src[3] : 0.f;
+          }
+        }
+      };
+      auto store_c = [&]() {
+        const int cl = tid >> 2, kk = (tid & 3) * 32;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          cs[kk + 4 * e][cl] = creg[e].x;
+          cs[kk + 4 * e + 1][cl] = creg[e].y;
+          cs[kk + 4 * e + 2][cl] = creg[e].z;
+          cs[kk + 4 * e + 3][cl] = creg[e].w;
+        }
+      };
+      // Rows of at most 128 dims are staged once for all centroid tiles.
+      const bool x_once = d <= kKK;
+      if (x_once) stage_rows<DT>(p, srow, 0, xs, xvec);
+      load_c(0, 0);
+      for (int c0 = 0; c0 < P; c0 += kKC) {
+        f4 acc[kKC / 16];
+#pragma unroll
+        for (int t = 0; t < kKC / 16; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int k0 = 0; k0 < d; k0 += kKK) {
+          if (!x_once) stage_rows<DT>(p, srow, k0, xs, xvec);
+          store_c();
+          __syncthreads();
+          // the next centroid tile's loads overlap this tile's matrix work
+          int nk0 = k0 + kKK, nc0 = c0;
+          if (nk0 >= d) {
+            nk0 = 0;
+            nc0 = c0 + kKC;
+          }
+          if (nc0 < P) load_c(nc0, nk0);
+          // lane (g, m) feeds A[row m][k g] and B[k g][centroid m]
 #pragma unroll 8
-      for (int ks = 0; ks < kKK; ks += 4) {
-        const float a = xs[wv * 16 + m][ks + g];
+          for (int ks = 0; ks < kKK; ks += 4) {
+            const float a = xs[wv * 16 + m][ks + g];
 #pragma unroll
-        for (int t = 0; t < kKC / 16; ++t)
-          acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, cs[ks + g][t * 16 + m], acc[t], 0, 0, 0);
+            for (int t = 0; t < kKC / 16; ++t)
+              acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, cs[ks + g][t * 16 + m], acc[t], 0, 0, 0);
+          }
+          __syncthreads();
+        }
+        // D layout: lane (g, m), register i -> row 4g + i, centroid t*16 + m.
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float s = -__builtin_inff();
+          int id = 0x7fffffff;
+#pragma unroll
+          for (int t = 0; t < kKC / 16; ++t) {
+            const int c = c0 + t * 16 + m;
+            if (c < P && beats(acc[t][i], c, s, id)) {
+              s = acc[t][i];
+              id = c;
+            }
+          }
+#pragma unroll
+          for (int off = 1; off < 16; off <<= 1) {
+            const float os = __shfl_xor(s, off, kWaveSize);
+            const int oid = __shfl_xor(id, off, kWaveSize);
+            if (beats(os, oid, s, id)) {
+              s = os;
+              id = oid;
+            }
+          }
+          if (beats(s, id, best[i], bid[i])) {
+            best[i] = s;
+            bid[i] = id;
+          }
+        }
       }
+      if (m == 0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int64_t row = row_of(wv * 16 + 4 * g + i);
+          if (row < p.n) {
+            p.assign[row] = bid[i];
+            if (p.score) p.score[row] = best[i];
+          }
+        }
+      }
+    }
+    if constexpr (LEFT) {
       __syncthreads();
+      c0row += (int64_t)gridDim.x * p.chunk;
     }
-    // D layout: lane (g, m), register i -> row 4g + i, centroid t*16 + m.
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float s = -__builtin_inff();
-      int id = 0x7fffffff;
-#pragma unroll
-      for (int t = 0; t < kKC / 16; ++t) {
-        const int c = c0 + t * 16 + m;
-        if (c < P && beats(acc[t][i], c, s, id)) {
-          s = acc[t][i];
-          id = c;
-        }
-      }
-#pragma unroll
-      for (int off = 1; off < 16; off <<= 1) {
-        const float os = __shfl_xor(s, off, kWaveSize);
-        const int oid = __shfl_xor(id, off, kWaveSize);
-        if (beats(os, oid, s, id)) {
-          s = os;
-          id = oid;
-        }
-      }
-      if (beats(s, id, best[i], bid[i])) {
-        best[i] = s;
-        bid[i] = id;
-      }
-    }
-  }
-  if (m == 0) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t row = r0 + wv * 16 + 4 * g + i;
-      if (row < p.n && (!p.only_left || p.assign[row] == -1)) {
-        p.assign[row] = bid[i];
-        if (p.score) p.score[row] = best[i];
-      }
-    }
-  }
-  __syncthreads();
-  }
+  } while (LEFT && c0row < p.n);
 }
 
 // Zero the fixed-point sums and the counts.
@@ -372,16 +400,20 @@ hipError_t launch_kmeans_assign(const KmeansParams &pin, const AssignParams *lef
                                 hipStream_t st) {
   if (pin.n == 0) return hipSuccess;
   KmeansParams p = pin;
-  int64_t blocks = (p.n + kKR - 1) / kKR;
-  if (left) {  // mostly a look at the ids: no more workgroups than run at once
-    p.only_left = 1;
+  if (left) {  // mostly a look at the ids: as many workgroups as run at once
     p.packed = left->packed;
-    blocks = blocks < 2LL * cus ? blocks : 2LL * cus;
+    const int64_t share = (p.n + 2LL * cus - 1) / (2LL * cus);
+    p.chunk = (int)std::min<int64_t>(kLeftChunk, (share + kKR - 1) / kKR * kKR);
+    const int64_t chunks = (p.n + p.chunk - 1) / p.chunk;
+    const dim3 grid((unsigned)std::min<int64_t>(chunks, 2LL * cus));
+    if (p.dtype == kF32) return launch1(dresd_kmeans_assign<kF32, true>, grid, dim3(256), p, st);
+    if (p.dtype == kF16) return launch1(dresd_kmeans_assign<kF16, true>, grid, dim3(256), p, st);
+    return launch1(dresd_kmeans_assign<kBF16, true>, grid, dim3(256), p, st);
   }
-  const dim3 grid((unsigned)blocks);
-  if (p.dtype == kF32) return launch1(dresd_kmeans_assign<kF32>, grid, dim3(256), p, st);
-  if (p.dtype == kF16) return launch1(dresd_kmeans_assign<kF16>, grid, dim3(256), p, st);
-  return launch1(dresd_kmeans_assign<kBF16>, grid, dim3(256), p, st);
+  const dim3 grid((unsigned)((p.n + kKR - 1) / kKR));
+  if (p.dtype == kF32) return launch1(dresd_kmeans_assign<kF32, false>, grid, dim3(256), p, st);
+  if (p.dtype == kF16) return launch1(dresd_kmeans_assign<kF16, false>, grid, dim3(256), p, st);
+  return launch1(dresd_kmeans_assign<kBF16, false>, grid, dim3(256), p, st);
 }
 
 hipError_t launch_kmeans_update(const KmeansParams &pin, int cus, hipStream_t st) {

@@ -132,8 +132,10 @@ struct KmeansParams {
   int32_t *cnt;              // [P] workspace (update)
   const uint32_t *sorted_row, *sorted_part;  // rows in partition order (update, may be null)
   int64_t offset;            // first picked row, in [0, n) (init)
-  int only_left;             // assign only the rows marked -1
-  const uint64_t *packed;    // ... after unpacking (score, id) keys [n], may be null
+  // assign only the rows marked -1, listed from this many rows at a time, after
+  // unpacking (score, id) keys [n] (may be null)
+  int chunk;
+  const uint64_t *packed;
 };
 // Assignment on the 16-bit matrix cores (dresd_assign.hip).
 struct AssignParams {

@@ -109,6 +109,31 @@ def test_rows_left_to_fp32(gpu_lib, dt, n, d, P):
     assert torch.equal(a[rest], ra[rest]) and torch.equal(sc[rest], rs[rest])
 
 
+@pytest.mark.parametrize("n,d,P,share", [(70001, 64, 300, 0.5), (600001, 40, 64, 0.3),
+                                         (1100000, 32, 4, 0.01), (4097, 200, 300, 1.0)])
+def test_many_rows_left_to_fp32(gpu_lib, n, d, P, share):
+    """Rows left over in every chunk, more than one block of 64 of them in
+    some: bit for bit as the fp32 contraction gives them, the others as without."""
+    from paper_2502_15572_amd import kmeans_assign
+    say("many rows left to fp32", n, d, P, share)
+    rng = np.random.default_rng(n + P)
+    keys = as_keys(unit(rng, n, d), "f16")
+    c = torch.from_numpy(unit(rng, P, d).astype(np.float32)).to(DEV)
+    left = rng.random(n) < share
+    left[: n // 3] &= np.arange(n // 3) % 97 == 0   # few there
+    dirty = keys.clone()
+    dirty[torch.from_numpy(left), 7] = float("inf")
+    a, sc = kmeans_assign(dirty.to(DEV), c, with_score=True)
+    ra, rs = kmeans_assign(keys.to(DEV), c, with_score=True)
+    wa, ws = kmeans_assign(_wide(dirty[torch.from_numpy(left)], d).to(DEV), _wide(c, d),
+                           with_score=True)
+    torch.cuda.synchronize()
+    left = torch.from_numpy(left).to(DEV)
+    assert torch.equal(a[left], wa)
+    assert torch.equal(sc[left].view(torch.int32), ws.view(torch.int32))
+    assert torch.equal(a[~left], ra[~left]) and torch.equal(sc[~left], rs[~left])
+
+
 @pytest.mark.parametrize("dt", ["f16", "bf16", "f32"])
 @pytest.mark.parametrize("value", [float("inf"), float("nan"), 3e38, 1e-25])
 def test_centroids_left_to_fp32(gpu_lib, dt, value):
