@@ -33,15 +33,16 @@ constexpr int kSmallMerge = 256;
 constexpr int kRankSortMax = 512;
 // Each thread looks at this many lists.
 constexpr int kListsPerThread = kMergeLists / kMergeThreads;
-// Work items of the gather (64 keys of a kept list each) held in LDS.
+// Work items of the gather (8, 16 or 64 keys of a kept list each) held in LDS.
 constexpr uint32_t kMergeItems = kMergeLists;
+static_assert(kMergeLists <= 4096, "items of 8 keys of all lists (at most 2,048 each) fit 21 bits");
 
 struct MergeShared {
   uint32_t hist[kMergeItems];  // radix histogram (256 bins); the gather's work items
   alignas(16) uint64_t cache[kMergeCap];
   alignas(16) uint64_t win[DRESD_K_MAX_INTERNAL];
-  uint64_t sel_prefix, sel_mask, bound, v_and, v_or;
-  uint32_t sel_krem, sel_done, win_cnt, ncand, total8, total64, known;
+  uint64_t sel_prefix, sel_mask, bound, v_and, v_or, items;
+  uint32_t sel_krem, sel_done, win_cnt, ncand, known;
 };
 
 __device__ inline uint64_t wave_and(uint64_t v) {
@@ -273,8 +274,7 @@ __global__ void __launch_bounds__(kMergeThreads) dresd_merge(MergeParams p) {
     sh.ncand = 0;
     sh.win_cnt = 0;
     sh.known = 0;
-    sh.total8 = 0;
-    sh.total64 = 0;
+    sh.items = 0;
   }
   __syncthreads();
   // Thread t looks at lists t, t + 1024, ...
@@ -315,37 +315,34 @@ __global__ void __launch_bounds__(kMergeThreads) dresd_merge(MergeParams p) {
   const uint64_t bnd = sh.bound;
 
   // 2. work items: 8 keys of a kept list (one whose best key reaches the
-  //    bound) for 8 lanes, so that short lists fill the loads too; 64 keys for
-  //    a wave where items of 8 would be too many.  In any order, eight rounds
-  //    of the workgroup in flight.
-  uint32_t items = 0;  // of 8 keys (low half) and of 64 (high half)
+  //    bound) for 8 lanes, so that short lists fill the loads too; 16 keys, or 64
+  //    for a wave, where smaller items would be too many.  In any order, eight
+  //    rounds of the workgroup in flight.
+  uint64_t items = 0;  // of 8, 16 and 64 keys, 21 bits each
 #pragma unroll
   for (int j = 0; j < kListsPerThread; ++j) {
     if (first[j] < bnd) cnt[j] = 0;
-    items += (cnt[j] + 7u) / 8u + ((cnt[j] + 63u) / 64u << 16);
+    items += (uint64_t)((cnt[j] + 7u) / 8u) | (uint64_t)((cnt[j] + 15u) / 16u) << 21 |
+             (uint64_t)((cnt[j] + 63u) / 64u) << 42;
   }
-  uint32_t lo = items & 0xffffu, hi = items >> 16;
+  uint64_t incl = items;
   for (int off = 1; off < kWaveSize; off <<= 1) {
-    const uint32_t v = __shfl_up(lo, off, kWaveSize), h = __shfl_up(hi, off, kWaveSize);
-    if (lane >= off) {
-      lo += v;
-      hi += h;
-    }
+    const uint64_t v = __shfl_up(incl, off, kWaveSize);
+    if (lane >= off) incl += v;
   }
-  uint32_t base8 = 0, base64 = 0;
-  if (lane == kWaveSize - 1 && lo) {
-    base8 = atomicAdd(&sh.total8, lo);
-    base64 = atomicAdd(&sh.total64, hi);
-  }
-  base8 = __shfl(base8, kWaveSize - 1, kWaveSize) + lo - (items & 0xffffu);
-  base64 = __shfl(base64, kWaveSize - 1, kWaveSize) + hi - (items >> 16);
+  uint64_t base = 0;
+  if (lane == kWaveSize - 1 && incl)
+    base = atomicAdd((unsigned long long *)&sh.items, (unsigned long long)incl);
+  base = __shfl(base, kWaveSize - 1, kWaveSize) + incl - items;
   __syncthreads();
-  const bool small = sh.total8 <= kMergeItems;
-  const uint32_t total = small ? sh.total8 : sh.total64;
-  const int lg = small ? 3 : 6;  // keys per item, as a power of two
+  const uint64_t all = sh.items;
+  const int level = ((uint32_t)all & 0x1fffffu) <= kMergeItems ? 0
+                    : ((uint32_t)(all >> 21) & 0x1fffffu) <= kMergeItems ? 1 : 2;
+  const uint32_t total = (uint32_t)(all >> (21 * level)) & 0x1fffffu;
+  const int lg = level == 0 ? 3 : level == 1 ? 4 : 6;  // keys per item, as a power of two
   const uint32_t per = 1u << lg;
   if (total <= kMergeItems) {
-    uint32_t at = small ? base8 : base64;
+    uint32_t at = (uint32_t)(base >> (21 * level)) & 0x1fffffu;
 #pragma unroll
     for (int j = 0; j < kListsPerThread; ++j)
       for (uint32_t c = 0; c < cnt[j]; c += per, ++at)
