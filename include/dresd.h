@@ -131,7 +131,9 @@ dresd_status dresd_index_create(const void *embeddings,
  * on one index from several host threads must be serialised by the caller.
  * Errors: EINVAL (null index/queries/idx/score, k out of range, B < 0),
  * ENOMEM (workspace growth failed; no output written), EUNSUPPORTED (the
- * workspace would have to grow during stream capture), EDEVICE.
+ * workspace would have to grow during stream capture), EDEVICE.  Small
+ * datastores list whole tiles, in a workspace of up to about 256 MiB; where
+ * that cannot be had, the scan with the shorter lists runs instead.
  */
 dresd_status dresd_search(dresd_index *ix, const float *queries, int32_t B,
                           int32_t k, int64_t *idx, float *score,
@@ -162,7 +164,8 @@ dresd_status dresd_search_filtered(dresd_index *ix, const float *queries,
  * code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  The same search as dresd_search (same kernels, bitwise the same
  * outputs; a batch of 1,024-dim keys whose tiled-contraction lists would
- * not fit the scratch runs the shared-key scan instead), with its workspace
+ * not fit the scratch runs the shared-key scan instead, and one whose lists
+ * of whole tiles would not fit the single-tile scan), with its workspace
  * in a fixed library scratch of
  * DRESD_SCRATCH_BYTES that every device the library runs on holds until the
  * process ends, instead of the index's growable workspace.  It allocates no

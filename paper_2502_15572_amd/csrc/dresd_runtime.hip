@@ -1085,8 +1085,22 @@ dresd_status search_impl(dresd_index *ix, const float *queries, const int32_t *n
                                     std::to_string(fixed_bytes) +
                                     " bytes of the fixed scratch (use dresd_search)");
   } else {
+    std::string before;
+    before.swap(g_err);
     s = ensure_workspace(ix, pl.bytes, st, &ws);
+    // Lists of whole tiles take up to 256 MiB, the single-tile scan's a
+    // quarter of it: it runs where they cannot be had (no memory, or they
+    // would have to grow inside a capture).
+    if ((s == DRESD_ENOMEM || s == DRESD_EUNSUPPORTED) && pl.small) {
+      Plan other;
+      if (make_plan(ix, B, k, other, next_tok != nullptr, true, true, false) == DRESD_OK &&
+          other.bytes < pl.bytes) {
+        pl = other;
+        s = ensure_workspace(ix, pl.bytes, st, &ws);
+      }
+    }
     if (s != DRESD_OK) return s;
+    g_err.swap(before);
   }
   const bool prof = ix->prof && !fixed;
   uint64_t *tau = reinterpret_cast<uint64_t *>(ws + pl.off_tau);

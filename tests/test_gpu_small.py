@@ -163,3 +163,59 @@ def test_small_search_without_allocation(gpu_lib, B):
     for a, b in zip(out, ref):
         assert torch.equal(a, b)
     ix.close()
+
+
+def _shorter_lists(B):
+    """262,144 x 128 fp32 keys: 48 queries' lists of whole tiles (195 MiB) take
+    more memory than the single-tile scan's (104 MiB, 136 for 128 queries)."""
+    from paper_2502_15572_amd import Index
+    keys, q, cont, _ = data("f32", 262144, 128, B, 11)
+    ix = Index(keys.to(DEV), torch.from_numpy(cont).to(DEV))
+    q = q.to(DEV)
+    return ix, q
+
+
+def test_small_search_without_memory_for_whole_tiles(gpu_lib):
+    """A search whose lists of whole tiles cannot be allocated runs with the
+    shorter lists, with the same results and no error left behind."""
+    from test_gpu_failure import fail_alloc_at
+    say("small search, no memory for whole tiles")
+    ix, q = _shorter_lists(48)
+    gpu_lib.dresd_search(None, None, 1, 1, None, None, None, None)
+    text = gpu_lib.dresd_last_error()
+    with fail_alloc_at(1):
+        got = ix.search(q, 10)
+    torch.cuda.synchronize()
+    assert gpu_lib.dresd_last_error() == text
+    for a, b in zip(got, ix.search(q, 10)):  # fp32 sums of the same products in the same order
+        assert torch.equal(a, b)
+    ix.close()
+
+
+def test_small_search_captured_after_a_larger_one(gpu_lib):
+    """The workspace of a warm-up at the largest batch serves the capture of a
+    smaller one, whose lists of whole tiles it does not hold."""
+    say("small search captured after a larger one")
+    ix, q = _shorter_lists(48)
+    rng = np.random.default_rng(12)
+    big = torch.from_numpy(unit(rng, 128, 128).astype(np.float32)).to(DEV)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        ix.search(big, 10, stream=s)
+    torch.cuda.synchronize()
+    assert ix.plan(128, 10)["workspace_bytes"] < ix.plan(48, 10)["workspace_bytes"]
+    out = (torch.empty((48, 10), dtype=torch.int64, device=DEV),
+           torch.empty((48, 10), dtype=torch.float32, device=DEV),
+           torch.empty((48, 10, 3), dtype=torch.int32, device=DEV))
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        ix.search(q, 10, out=out, stream=s)
+    want = ix.search(q, 10)
+    for _ in range(3):
+        for t in out:
+            t.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(out, want):
+            assert torch.equal(a, b)
+    ix.close()
