@@ -44,9 +44,10 @@ extern "C" {
  * A call that would have to grow a workspace while its stream is being
  * captured fails with DRESD_EUNSUPPORTED instead.  A workspace that a later,
  * larger call outgrows is never freed before its owner is (the index for
- * search workspaces, the process for the transform and k-means buffers, one
- * per device and stream), so a graph captured earlier stays valid after such
- * a call.
+ * search workspaces, the process for the sums of transforms and k-means
+ * updates, one per device and stream), so a graph captured earlier stays
+ * valid after such a call.  (Buffers that only uncaptured calls use are freed
+ * when outgrown and by dresd_release_cached.)
  *
  * Allocation-failure test hook: with DRESD_FAIL_ALLOC_AT=n in the
  * environment, the n-th device allocation the library makes (counted from
@@ -195,11 +196,25 @@ dresd_status dresd_index_info(const dresd_index *ix, int64_t *N, int32_t *d,
                               int32_t *L, int32_t *dtype);
 
 /* Free an index and its workspace (synchronises its device).  NULL is
- * ignored.  Blocks of keys and values of at least 64 MiB are kept for the
- * next index that is created, together at most 1/128 of the device's memory (the oldest go
- * back to the driver first, all of them when an allocation of the library
- * fails); larger ones and everything smaller go back at once. */
+ * ignored.  Blocks of at least 64 MiB that held its keys, values, first tokens
+ * or (partitioned) slot tables, or the memory that grouped the rows of a build,
+ * are kept for the next index that is created, together at most 1/128 of the
+ * device's memory: the oldest go back to the driver first, and all of a
+ * device's go back when an allocation of the library on it fails and they
+ * would make room for it, or by dresd_release_cached.  Larger blocks and
+ * everything smaller go back at once. */
 void dresd_index_destroy(dresd_index *ix);
+
+/* Give back to the driver the device memory that the library holds for later
+ * calls and that neither an index nor a captured graph uses: the blocks kept
+ * by dresd_index_destroy and dresd_ivf_destroy, and the operands and sorting
+ * buffers of uncaptured transforms, k-means assignments and updates (at most
+ * 256 MiB each per device and stream), on every device.  For programs whose
+ * other allocators need the memory.  Synchronises the devices concerned; may be
+ * called from any thread, but not while a stream is being captured.  Later
+ * calls allocate again what they need.
+ * Errors: EDEVICE, ENOMEM (the host's). */
+dresd_status dresd_release_cached(void);
 
 /* Message for the last failing call on this thread ("" if none).  The
  * pointer stays valid until the next call on this thread. */
@@ -260,8 +275,8 @@ dresd_status dresd_bw_probe(const void *buf, int64_t bytes, int32_t reps, int32_
  * Arithmetic: fp32, the projection on the fp32 matrix cores, or for large
  * batches (at least 512 rows and about 2^30 multiply-adds) on the 16-bit ones
  * with z and W in three bf16 parts each that sum to them (error no larger; a
- * workspace of 6 D l bytes, at most 256 MiB; in fp32 without it and inside a
- * capture, whose graph may replay on any stream); batches with
+ * workspace of 6 D l bytes, at most 256 MiB, kept for later calls; in fp32
+ * without it and inside a capture, whose graph may replay on any stream); batches with
  * few output tiles split D across workgroups and add the partial sums in a
  * fixed order, so results are deterministic.  Ownership: all buffers are
  * caller-owned and must stay alive until `stream` completes; the partial sums
@@ -423,8 +438,8 @@ dresd_status dresd_ivf_search_next_token(dresd_ivf *ivf, const float *queries,
  *   assign device [n] int32 out; score device [n] fp32 out.  Rows of at most
  *   256 dims are multiplied on the 16-bit matrix cores (the centroids split
  *   into three exact parts) with a workspace of about 6 P d bytes (at most
- *   256 MiB; 8 n more for small n) per (device, stream), kept as for
- *   dresd_kmeans_update; a call that cannot get one, or that is captured (its
+ *   256 MiB; 8 n more for small n) per (device, stream), kept for later
+ *   calls; a call that cannot get one, or that is captured (its
  *   graph may replay on any stream), runs in fp32 without.
  * dresd_kmeans_update: each centroid becomes the unit vector along the sum of
  *   the rows assigned to it; a centroid with no rows (or a zero sum) is left
@@ -432,11 +447,11 @@ dresd_status dresd_ivf_search_next_token(dresd_ivf *ivf, const float *queries,
  *   order of the rows (deterministic).  x as above with n < 2^31; assign
  *   device [n] int32, each in [0, P) (not checked: the caller's contract);
  *   centroids device [P, d] fp32 in/out; counts device [P] int32 out (rows per
- *   centroid, NULL allowed).  Uses a workspace of P*d*8 + P*4 bytes (and, from
- *   2^24 elements to 2^24 rows, where it can be had and outside captures, 16 n
- *   more to sort them) per
+ *   centroid, NULL allowed).  Uses a workspace of P*d*8 + P*4 bytes per
  *   (device, stream), allocated (synchronously) on first use on that stream
- *   and kept, like every buffer it outgrows, until the process ends: calls
+ *   and kept, like every buffer it outgrows, until the process ends (and, from
+ *   2^24 elements to 2^24 rows, where it can be had and outside captures, 16 n
+ *   more to sort them, kept for later calls): calls
  *   on different streams may overlap, calls on one stream are ordered by it,
  *   also when several host threads make them.  A graph captured from an
  *   update uses that stream's buffer of sums: it must not replay beside

@@ -15,7 +15,8 @@ from . import _lib
 from ._lib import DresdError, K_MAX  # noqa: F401
 
 __all__ = ["Index", "PartitionedIndex", "DresdError", "K_MAX", "transform", "pack_drafts",
-           "kmeans_assign", "kmeans_update", "kmeans_init", "train_partitions", "bw_probe"]
+           "kmeans_assign", "kmeans_update", "kmeans_init", "train_partitions", "bw_probe",
+           "release_cached"]
 
 _DTYPES = None
 
@@ -430,6 +431,13 @@ def train_partitions(x, P: int, iters: int = 10, seed: int = 0, stream=None):
         assign = kmeans_assign(x, centroids, stream=stream)
         kmeans_update(x, assign, centroids, stream)
     return centroids, kmeans_assign(x, centroids, stream=stream)
+
+
+def release_cached() -> None:
+    """Give back the device memory that the library holds for later calls
+    (large blocks of closed indexes, operand and sorting buffers), for a program
+    whose other allocators need it.  Not while a stream is being captured."""
+    _lib.check(_lib.load().dresd_release_cached())
 
 
 def bw_probe(buf, reps: int = 10, workgroups: int = 0, stream=None) -> float:

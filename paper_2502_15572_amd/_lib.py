@@ -24,7 +24,8 @@ EXPORTS = ["dresd_index_create", "dresd_search", "dresd_index_info", "dresd_inde
            "dresd_ivf_search", "dresd_ivf_search_filtered", "dresd_ivf_search_probes",
            "dresd_ivf_create_by_token", "dresd_ivf_search_next_token", "dresd_ivf_profile_enable",
            "dresd_ivf_profile_read", "dresd_kmeans_assign", "dresd_kmeans_update",
-           "dresd_kmeans_init", "dresd_bw_probe", "dresd_search_noalloc"]
+           "dresd_kmeans_init", "dresd_bw_probe", "dresd_search_noalloc",
+           "dresd_release_cached"]
 
 _lock = threading.Lock()
 _lib = None
@@ -83,6 +84,8 @@ def _declare(lib):
     lib.dresd_index_info.restype = ctypes.c_int
     lib.dresd_index_destroy.argtypes = [P]
     lib.dresd_index_destroy.restype = None
+    lib.dresd_release_cached.argtypes = []
+    lib.dresd_release_cached.restype = ctypes.c_int
     lib.dresd_last_error.argtypes = []
     lib.dresd_last_error.restype = ctypes.c_char_p
     lib.dresd_profile_enable.argtypes = [P, I32]

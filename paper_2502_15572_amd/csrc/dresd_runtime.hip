@@ -68,12 +68,17 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Large blocks that destroyed indexes and finished builds gave up, kept for
 // the next build.  The driver wipes released memory at about 35 GB/s and makes
-// hipFree wait for it: rebuilding a 1.3 GB index in a loop spent 31 of 38 ms
-// there.  Bounded: blocks of at least 64 MiB, together at most 1/128 of the
-// device's memory (2.25 GiB of 288), the oldest released first; all of them
-// are released as soon as an allocation fails.  A block is kept only after the
-// device has finished with it (as hipFree would wait), so it may be used again
-// on any stream and from any thread.
+// hipFree, or the next allocation, wait for it: rebuilding a 1.3 GB index in a
+// loop spent up to 31 of 38 ms there.  Build and close of 4,194,304 x 128 f16 keys
+// grouped by first token 1.24 ms, 2.09 with everything given back in between;
+// 16,777,216 ungrouped 2.6, 130 given back; 33,554,432 (8.6 GB, past the bound)
+// 55 to 830 either way.  Bounded: blocks of at least 64 MiB, together at most 1/128 of the
+// device's memory (2.25 GiB of 288: the keys, values, tables and sort memory of
+// an index of about 2 GB), the oldest released first.  A device's blocks are
+// all released when an allocation of the library fails and they would make the
+// room for it, and when the program asks (dresd_release_cached).  A block is
+// kept only after the device has finished with it (as hipFree would wait), so it
+// may be used again on any stream and from any thread.
 struct BlockCache {
   static constexpr size_t kMinBlock = (size_t)64 << 20;
   struct Block {
@@ -100,6 +105,13 @@ struct BlockCache {
       else kept[n++] = b;
     }
     kept.resize(n);
+  }
+  // Every device's blocks (the caller restores its current device).
+  void release_all() {
+    std::lock_guard<std::mutex> lock(mu);
+    for (const Block &b : kept)
+      if (hipSetDevice(b.dev) == hipSuccess) (void)hipFree(b.ptr);
+    kept.clear();
   }
   hipError_t take(void **ptr, size_t bytes, bool keep) {
     *ptr = nullptr;
@@ -693,26 +705,51 @@ dresd_status ensure_workspace(dresd_index *ix, size_t bytes, hipStream_t st,
   return DRESD_OK;
 }
 
-// Library buffers kept until the process ends (the transform's partial
-// sums, the k-means sums), one per (device, stream): calls on different
-// streams never share one, and calls on one stream are ordered by it.  A
-// call's kernels only find in the buffer what the call's own earlier kernels
-// wrote if no other call's kernels come between them on the stream: a call
-// holds its buffer's lock until its last kernel is launched, so host threads
-// that share a stream (torch's default stream is one for all threads) take
-// turns.  A buffer grows (allocating synchronously) when a call needs more;
-// the one it outgrows is kept as well, because a graph captured from an
-// earlier call may still replay on it.
+// Library buffers kept between calls, one per (device, stream): calls on
+// different streams never share one, and calls on one stream are ordered by
+// it.  A call's kernels only find in the buffer what the call's own earlier
+// kernels wrote if no other call's kernels come between them on the stream: a
+// call holds its buffer's lock until its last kernel is launched, so host
+// threads that share a stream (torch's default stream is one for all threads)
+// take turns.  A buffer grows (allocating synchronously) when a call needs more.
+// Buffers that captured calls use as well (the transform's partial sums, the
+// k-means sums) stay until the process ends, and so do those they outgrow,
+// because a graph may still replay on them.  The others (up to 256 MiB each)
+// only serve uncaptured calls: they are released when outgrown and when the
+// program asks (dresd_release_cached).
 struct DeviceBuffers {
   struct Buffer {
     std::mutex use;
     void *ptr = nullptr;
     size_t bytes = 0;
   };
+  const bool in_graphs;
   std::mutex mu;  // of the map and of retired
   std::map<std::pair<int, hipStream_t>, Buffer> cur;
   std::vector<void *> retired;
+  explicit DeviceBuffers(bool graphs) : in_graphs(graphs) {}
+  // The memory of every buffer that no graph uses, each when no call is
+  // enqueueing its kernels around it (the caller restores its current device).
+  void release() {
+    std::vector<std::pair<int, Buffer *>> all;
+    {
+      std::lock_guard<std::mutex> lock(mu);
+      for (auto &c : cur) all.emplace_back(c.first.first, &c.second);
+    }
+    for (auto &b : all) {
+      std::lock_guard<std::mutex> use(b.second->use);
+      if (!b.second->ptr || hipSetDevice(b.first) != hipSuccess) continue;
+      (void)hipDeviceSynchronize();
+      dev_free(b.second->ptr);
+      b.second->ptr = nullptr;
+      b.second->bytes = 0;
+    }
+  }
 };
+// Partial sums of transforms with D split and sums of k-means updates; operands
+// of large transforms and of assignments, and sorted rows of updates.
+DeviceBuffers g_transform_sums(true), g_update_sums(true);
+DeviceBuffers g_transform_ops(false), g_assign_ops(false), g_update_sort(false);
 
 // The buffer for (dev, st), at least `need` bytes, with its lock in `use`.
 dresd_status device_buffer(DeviceBuffers &db, int dev, size_t need, hipStream_t st,
@@ -736,9 +773,12 @@ dresd_status device_buffer(DeviceBuffers &db, int dev, size_t need, hipStream_t 
     void *old = c->ptr;
     c->ptr = b;
     c->bytes = need;
-    if (old) {
+    if (old && db.in_graphs) {
       std::lock_guard<std::mutex> lock(db.mu);
       db.retired.push_back(old);
+    } else if (old) {
+      (void)hipDeviceSynchronize();  // calls on the stream may still use it
+      dev_free(old);
     }
   }
   *out = c->ptr;
@@ -976,6 +1016,17 @@ void dresd_index_destroy(dresd_index *ix) {
   for (auto e : profile_events(ix)) (void)hipEventDestroy(e);
   (void)hipSetDevice(cur);
   delete ix;
+}
+
+dresd_status dresd_release_cached(void) try {
+  int cur = 0;
+  DRESD_HIP(hipGetDevice(&cur));
+  block_cache().release_all();
+  for (DeviceBuffers *db : {&g_transform_ops, &g_assign_ops, &g_update_sort}) db->release();
+  DRESD_HIP(hipSetDevice(cur));
+  return DRESD_OK;
+} catch (const std::bad_alloc &) {  // the host's own lists
+  return DRESD_ENOMEM;
 }
 
 dresd_status dresd_search_plan(const dresd_index *cix, int32_t B, int32_t k, int32_t *sample_passes,
@@ -1289,7 +1340,6 @@ dresd_status dresd_transform(const float *x, int64_t M, int32_t D, const float *
   DRESD_HIP(hipGetDevice(&dev));
   int cus = 0;
   DRESD_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-  static DeviceBuffers bufs, split_bufs;
   hipStream_t st = static_cast<hipStream_t>(stream);
   TransformParams p;
   p.splits = transform_splits(M, D, l, cus);
@@ -1301,10 +1351,11 @@ dresd_status dresd_transform(const float *x, int64_t M, int32_t D, const float *
     std::unique_lock<std::mutex> use;  // of the workspace, until the launches are made
     void *b = nullptr;
     // A later capture of this shape runs in fp32 and cannot allocate.
-    if (p.splits > 1) (void)device_buffer(bufs, dev, need, st, "transform workspace", &b, use);
+    if (p.splits > 1)
+      (void)device_buffer(g_transform_sums, dev, need, st, "transform workspace", &b, use);
     use = {};
-    if (device_buffer(split_bufs, dev, (size_t)pp.bytes, st, "transform workspace", &b, use) ==
-        DRESD_OK) {
+    if (device_buffer(g_transform_ops, dev, (size_t)pp.bytes, st, "transform workspace", &b,
+                      use) == DRESD_OK) {
       pp.t.x = x;
       pp.t.mean = mean;
       pp.t.var = var;
@@ -1326,7 +1377,8 @@ dresd_status dresd_transform(const float *x, int64_t M, int32_t D, const float *
     // Partial sums of the D slices (a per-device buffer kept for the life of
     // the process).
     void *b = nullptr;
-    dresd_status s = device_buffer(bufs, dev, need, st, "transform workspace", &b, use);
+    dresd_status s =
+        device_buffer(g_transform_sums, dev, need, st, "transform workspace", &b, use);
     if (s != DRESD_OK) return s;
     p.part = static_cast<float *>(b);
   }
@@ -1960,11 +2012,10 @@ dresd_status dresd_kmeans_assign(const void *x, int64_t n, int32_t d, int32_t dt
   AssignParams ap;
   if (n * (int64_t)P * d >= kAssignSplitWork && may_use_buffer(st) &&
       assign_split_plan(n, d, dtype, P, cus, &ap)) {
-    static DeviceBuffers bufs;
     std::unique_lock<std::mutex> use;  // of the workspace, until the launches are made
     void *ws = nullptr;
-    if (device_buffer(bufs, dev, (size_t)ap.bytes, st, "k-means assignment workspace", &ws, use) ==
-        DRESD_OK) {
+    if (device_buffer(g_assign_ops, dev, (size_t)ap.bytes, st, "k-means assignment workspace", &ws,
+                      use) == DRESD_OK) {
       ap.x = x;
       ap.centroids = centroids;
       ap.assign = assign;
@@ -1990,15 +2041,13 @@ dresd_status dresd_kmeans_update(const void *x, int64_t n, int32_t d, int32_t dt
   DRESD_HIP(hipGetDevice(&dev));
   int cus = 0;
   DRESD_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-  // Fixed-point sums and counts (a per-device buffer kept for the life of
-  // the process).
-  static DeviceBuffers bufs;
+  // Fixed-point sums and counts (a buffer kept for the life of the process).
   const size_t need = (size_t)P * d * 8 + (size_t)P * 4;
   void *wsp = nullptr;
   hipStream_t st = static_cast<hipStream_t>(stream);
   // of the two buffers, always taken in this order, until the launches are made
   std::unique_lock<std::mutex> use, sort_use;
-  dresd_status s = device_buffer(bufs, dev, need, st, "k-means workspace", &wsp, use);
+  dresd_status s = device_buffer(g_update_sums, dev, need, st, "k-means workspace", &wsp, use);
   if (s != DRESD_OK) return s;
   KmeansParams p = {};
   // Many elements: rows sorted by partition first, so that a partition's sum
@@ -2008,14 +2057,13 @@ dresd_status dresd_kmeans_update(const void *x, int64_t n, int32_t d, int32_t dt
   // (100,000 x 64: 77 against 61 us).  Without a workspace for the
   // sort (no memory, or inside a capture), or with more rows than 256 MiB of
   // it holds, in row order.
-  static DeviceBuffers sort_bufs;
   GroupParams gp = {};
   gp.n = n;
   gp.nblk = ceil_div(n, kGroupTile);
   const size_t seq = ((size_t)n * 4 + 255) / 256 * 256;
   void *sp = nullptr;
   if (n * (int64_t)d >= kSortedUpdateWork && n <= (int64_t)1 << 24 && may_use_buffer(st) &&
-      device_buffer(sort_bufs, dev, 4 * seq + 8192 + (size_t)gp.nblk * 1024, st,
+      device_buffer(g_update_sort, dev, 4 * seq + 8192 + (size_t)gp.nblk * 1024, st,
                     "k-means sort workspace", &sp, sort_use) == DRESD_OK) {
     unsigned char *b = static_cast<unsigned char *>(sp);
     for (int i = 0; i < 2; ++i) {
