@@ -330,8 +330,11 @@ dresd_status dresd_pack_drafts(const int32_t *tokens, int32_t B, int32_t k, int3
  * 3 = tiled contraction (keys of more than 1,024 dims at batches of two or
  * more query tiles, and 1,024-dim keys at batches past four query tiles: key
  * and query blocks both streamed through LDS, column by column, for panels
- * of 16 or 32 key tiles), and the number of launches of the main scan (each
- * one pass over the keys for a part of the batch).
+ * of 16 or 32 key tiles), 4 = whole-tile scan (small datastores with fp32
+ * keys, or with 16-bit keys at batches of at most four queries: every key of a
+ * wave's one, two or four tiles is listed for the merge), and the number of
+ * launches of the main scan (each one pass over the keys for a part of the
+ * batch).
  * Errors: EINVAL for the same argument errors as dresd_search.
  */
 dresd_status dresd_search_plan(const dresd_index *ix, int32_t B, int32_t k,

@@ -38,7 +38,8 @@ def _stream_handle(stream=None):
 
 
 # dresd_search_plan's scan kinds
-SCAN_KINDS = {0: "single_tile", 1: "shared_key", 2: "single_tile_grouped", 3: "tiled"}
+SCAN_KINDS = {0: "single_tile", 1: "shared_key", 2: "single_tile_grouped", 3: "tiled",
+              4: "whole_tile"}
 
 
 class Index:

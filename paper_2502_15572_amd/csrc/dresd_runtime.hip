@@ -1047,9 +1047,11 @@ dresd_status dresd_search_plan(const dresd_index *cix, int32_t B, int32_t k, int
   const Group g0 = group_of(pl, 0);
   if (sample_passes) *sample_passes = (int32_t)pl.npass;
   if (scan_waves)
-    *scan_waves = (int32_t)(pass_wgs(pl, g0, ix->T) * g0.ng * (threads_of(pl, true) / kWaveSize));
+    *scan_waves = (int32_t)((pl.small ? (int64_t)pl.wg_max * pl.qt
+                                      : pass_wgs(pl, g0, ix->T) * g0.ng) *
+                            (threads_of(pl, true) / kWaveSize));
   if (workspace_bytes) *workspace_bytes = (int64_t)pl.bytes;
-  if (scan_kind) *scan_kind = pl.tc ? 3 : pl.mq ? 1 : (g0.ng > 1 ? 2 : 0);
+  if (scan_kind) *scan_kind = pl.small ? 4 : pl.tc ? 3 : pl.mq ? 1 : (g0.ng > 1 ? 2 : 0);
   if (launches) *launches = (int32_t)pl.nl;
   return DRESD_OK;
 }

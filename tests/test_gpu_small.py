@@ -51,6 +51,7 @@ def test_small_search(gpu_lib, dt, N, d, B, k):
     kb, kdt = to_numpy_bits(keys)
     qn = q.numpy()
     ix = Index(keys.to(DEV), torch.from_numpy(cont).to(DEV))
+    assert ix.plan(B, k)["scan_kernel"] == "whole_tile"
     ntd = torch.from_numpy(nt).to(DEV)
     for filt in (False, True):
         idx, score, tok = ix.search(q.to(DEV), k, next_tok=ntd if filt else None)
@@ -218,4 +219,34 @@ def test_small_search_captured_after_a_larger_one(gpu_lib):
         torch.cuda.synchronize()
         for a, b in zip(out, want):
             assert torch.equal(a, b)
+    ix.close()
+
+
+@pytest.mark.parametrize("dt,N,d,B,waves", [
+    ("f32", 1, 1, 1, 4),              # one tile, one workgroup
+    ("f32", 262144, 144, 1, None),    # past 2^17 blocks of keys
+    ("f32", 262144, 128, 1, 4096),    # 2^17 blocks, four tiles per wave
+    ("f32", 262145, 16, 1, None),     # past the lists that the merge takes
+    ("f32", 16384, 512, 129, 9216),   # nine query tiles; 32 blocks per tile
+    ("f32", 16384, 513, 1, None),     # 33 blocks per tile
+    ("f32", 262144, 16, 64, 16384),   # 2^20 (query, tile) pairs
+    ("f32", 262144, 16, 65, None),
+    ("f16", 16384, 128, 4, 1024),
+    ("f16", 16384, 128, 5, None),     # past four queries of 16-bit keys
+    ("bf16", 16384, 1024, 4, 1024),
+    ("bf16", 16384, 1025, 4, None),
+])
+def test_shapes_of_the_whole_tile_scan(gpu_lib, dt, N, d, B, waves):
+    """The plan names the whole-tile scan, with the waves of its launch, just
+    inside the limits of its rule and another scan just outside."""
+    from paper_2502_15572_amd import Index
+    say("shapes of the whole-tile scan", dt, N, d, B)
+    ix = Index(torch.zeros(N, d, dtype={"f32": torch.float32, "f16": torch.float16,
+                                        "bf16": torch.bfloat16}[dt], device=DEV),
+               torch.zeros(N, 1, dtype=torch.int32, device=DEV))
+    plan = ix.plan(B, 1)
+    assert (plan["scan_kernel"] == "whole_tile") == (waves is not None)
+    if waves is not None:
+        assert plan["scan_waves"] == waves and plan["launches"] == 1
+        assert plan["sample_passes"] == 0
     ix.close()
