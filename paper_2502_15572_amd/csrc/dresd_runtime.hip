@@ -58,6 +58,14 @@ dresd_status fail(dresd_status s, const std::string &msg) {
   return s;
 }
 
+// Puts the thread's error text back as it was, for a step whose failure the
+// call gets over (it goes on without the step and succeeds).
+struct KeepError {
+  std::string before;
+  KeepError() { before.swap(g_err); }
+  void restore() { g_err.swap(before); }
+};
+
 #define DRESD_HIP(call)                                                              \
   do {                                                                               \
     hipError_t e_ = (call);                                                          \
@@ -784,6 +792,7 @@ dresd_status device_buffer(DeviceBuffers &db, int dev, size_t need, hipStream_t 
   *out = c->ptr;
   return DRESD_OK;
 } catch (const std::bad_alloc &) {  // the host's own lists
+  g_err.clear();
   return DRESD_ENOMEM;
 }
 
@@ -1138,8 +1147,7 @@ dresd_status search_impl(dresd_index *ix, const float *queries, const int32_t *n
                                     std::to_string(fixed_bytes) +
                                     " bytes of the fixed scratch (use dresd_search)");
   } else {
-    std::string before;
-    before.swap(g_err);
+    KeepError error;
     s = ensure_workspace(ix, pl.bytes, st, &ws);
     // Lists of whole tiles take up to 256 MiB, the single-tile scan's a
     // quarter of it: it runs where they cannot be had (no memory, or they
@@ -1153,7 +1161,7 @@ dresd_status search_impl(dresd_index *ix, const float *queries, const int32_t *n
       }
     }
     if (s != DRESD_OK) return s;
-    g_err.swap(before);
+    error.restore();
   }
   const bool prof = ix->prof && !fixed;
   uint64_t *tau = reinterpret_cast<uint64_t *>(ws + pl.off_tau);
@@ -1350,14 +1358,17 @@ dresd_status dresd_transform(const float *x, int64_t M, int32_t D, const float *
   // weight operands (no memory, or inside a capture) in fp32.
   ProjectParams pp;
   if (may_use_buffer(st) && project_split_plan(M, D, l, cus, &pp)) {
+    KeepError error;
     std::unique_lock<std::mutex> use;  // of the workspace, until the launches are made
     void *b = nullptr;
     // A later capture of this shape runs in fp32 and cannot allocate.
     if (p.splits > 1)
       (void)device_buffer(g_transform_sums, dev, need, st, "transform workspace", &b, use);
     use = {};
-    if (device_buffer(g_transform_ops, dev, (size_t)pp.bytes, st, "transform workspace", &b,
-                      use) == DRESD_OK) {
+    const dresd_status s =
+        device_buffer(g_transform_ops, dev, (size_t)pp.bytes, st, "transform workspace", &b, use);
+    error.restore();
+    if (s == DRESD_OK) {
       pp.t.x = x;
       pp.t.mean = mean;
       pp.t.var = var;
@@ -2014,10 +2025,13 @@ dresd_status dresd_kmeans_assign(const void *x, int64_t n, int32_t d, int32_t dt
   AssignParams ap;
   if (n * (int64_t)P * d >= kAssignSplitWork && may_use_buffer(st) &&
       assign_split_plan(n, d, dtype, P, cus, &ap)) {
+    KeepError error;
     std::unique_lock<std::mutex> use;  // of the workspace, until the launches are made
     void *ws = nullptr;
-    if (device_buffer(g_assign_ops, dev, (size_t)ap.bytes, st, "k-means assignment workspace", &ws,
-                      use) == DRESD_OK) {
+    const dresd_status s = device_buffer(g_assign_ops, dev, (size_t)ap.bytes, st,
+                                         "k-means assignment workspace", &ws, use);
+    error.restore();
+    if (s == DRESD_OK) {
       ap.x = x;
       ap.centroids = centroids;
       ap.assign = assign;
@@ -2064,9 +2078,14 @@ dresd_status dresd_kmeans_update(const void *x, int64_t n, int32_t d, int32_t dt
   gp.nblk = ceil_div(n, kGroupTile);
   const size_t seq = ((size_t)n * 4 + 255) / 256 * 256;
   void *sp = nullptr;
-  if (n * (int64_t)d >= kSortedUpdateWork && n <= (int64_t)1 << 24 && may_use_buffer(st) &&
-      device_buffer(g_update_sort, dev, 4 * seq + 8192 + (size_t)gp.nblk * 1024, st,
-                    "k-means sort workspace", &sp, sort_use) == DRESD_OK) {
+  if (n * (int64_t)d >= kSortedUpdateWork && n <= (int64_t)1 << 24 && may_use_buffer(st)) {
+    KeepError error;
+    if (device_buffer(g_update_sort, dev, 4 * seq + 8192 + (size_t)gp.nblk * 1024, st,
+                      "k-means sort workspace", &sp, sort_use) != DRESD_OK)
+      sp = nullptr;
+    error.restore();
+  }
+  if (sp) {
     unsigned char *b = static_cast<unsigned char *>(sp);
     for (int i = 0; i < 2; ++i) {
       gp.key[i] = reinterpret_cast<uint32_t *>(b + (size_t)(2 * i) * seq);
