@@ -208,8 +208,8 @@ void dresd_index_destroy(dresd_index *ix);
 /* Give back to the driver the device memory that the library holds for later
  * calls and that neither an index nor a captured graph uses: the blocks kept
  * by dresd_index_destroy and dresd_ivf_destroy, and the operands and sorting
- * buffers of uncaptured transforms, k-means assignments and updates (at most
- * 256 MiB each per device and stream), on every device.  For programs whose
+ * buffers of uncaptured transforms (at most 512 MiB per device and stream),
+ * k-means assignments and updates (256 MiB each), on every device.  For programs whose
  * other allocators need the memory.  Synchronises the devices concerned; may be
  * called from any thread, but not while a stream is being captured.  Later
  * calls allocate again what they need.
@@ -275,7 +275,8 @@ dresd_status dresd_bw_probe(const void *buf, int64_t bytes, int32_t reps, int32_
  * Arithmetic: fp32, the projection on the fp32 matrix cores, or for large
  * batches (at least 512 rows and about 2^30 multiply-adds) on the 16-bit ones
  * with z and W in three bf16 parts each that sum to them (error no larger; a
- * workspace of 6 D l bytes, at most 256 MiB, kept for later calls; in fp32
+ * workspace of 6 D l bytes, at most 256 MiB, and as much again at most for
+ * partial sums, kept for later calls; in fp32
  * without it and inside a capture, whose graph may replay on any stream); batches with
  * few output tiles split D across workgroups and add the partial sums in a
  * fixed order, so results are deterministic.  Ownership: all buffers are

@@ -520,10 +520,12 @@ bool project_split_plan(int64_t M, int D, int l, int cus, ProjectParams *out) {
   if (op > most) return false;
   // One workgroup per CU runs at once.  D is split where that shortens the
   // rounds of workgroups times a slice's blocks of dims (and about 6 blocks'
-  // time to start and end), into slices of at least 4 blocks.
+  // time to start and end), into slices of at least 4 blocks whose partial sums
+  // take at most 256 MiB.
   const int64_t wgs = (M + kPRows - 1) / kPRows * p.groups;
   int64_t best = 0;
-  for (int s = 1; s <= 64 && (s == 1 || (s * 4 <= p.KB && wgs < 2 * cus)); ++s) {
+  for (int s = 1; s <= 64 && (s == 1 || (s * 4 <= p.KB && wgs < 2 * cus &&
+                                         s * M * l * 4 <= most)); ++s) {
     const int64_t cost = (wgs * s + cus - 1) / cus * ((p.KB + s - 1) / s + 6);
     if (s == 1 || cost < best) {
       best = cost;

@@ -722,8 +722,8 @@ dresd_status ensure_workspace(dresd_index *ix, size_t bytes, hipStream_t st,
 // take turns.  A buffer grows (allocating synchronously) when a call needs more.
 // Buffers that captured calls use as well (the transform's partial sums, the
 // k-means sums) stay until the process ends, and so do those they outgrow,
-// because a graph may still replay on them.  The others (up to 256 MiB each)
-// only serve uncaptured calls: they are released when outgrown and when the
+// because a graph may still replay on them.  The others (up to 256 MiB
+// each, 512 a transform's) only serve uncaptured calls: they are released when outgrown and when the
 // program asks (dresd_release_cached).
 struct DeviceBuffers {
   struct Buffer {

@@ -101,3 +101,26 @@ def test_buffers_of_uncaptured_calls(gpu_lib):
     torch.cuda.empty_cache()
     assert before - free_bytes() <= _hold + SLACK
     _release()
+
+
+def test_transform_workspace_is_bounded(gpu_lib):
+    """Partial sums of a batch that is split over D take at most 256 MiB (eight
+    slices, which the split would take otherwise, 264) beside the operands."""
+    from paper_2502_15572_amd import transform
+    say("transform workspace")
+    M, D, l = 8448, 16384, 1024
+    x = torch.randn(M, D, device=DEV)
+    mean, var = torch.zeros(D, device=DEV), torch.ones(D, device=DEV)
+    W = torch.randn(D, l, device=DEV) / 128
+    out = torch.empty(M, l, device=DEV)
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        transform(x[:600], mean, var, W, out=out[:600], stream=s)  # loads the kernels
+    _release()
+    before = free_bytes()
+    with torch.cuda.stream(s):
+        transform(x, mean, var, W, out=out, stream=s)
+    torch.cuda.synchronize()
+    assert 6 * D * l <= before - free_bytes() <= 6 * D * l + (256 << 20) + SLACK
+    _release()
