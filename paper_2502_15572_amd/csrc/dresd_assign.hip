@@ -6,7 +6,8 @@
 //   f16 keys : hi, mid, lo in f16 of the centroid scaled by a power of two
 //              that brings its largest element to [2^14, 2^15) (all three
 //              parts at one scale, so one accumulator takes them; what is cut
-//              off is below 2^-40 of the largest element); 3 products.
+//              off is at most 2^-25 there: 2^-39 of the largest element); 3
+//              products.
 //   bf16 keys: hi, mid, lo in bf16 (8 + 8 + 8 bits: the fp32 centroid); 3
 //              products.
 //   fp32 keys: rows split the same way; the six products of parts whose
@@ -425,7 +426,7 @@ bool assign_split_plan(int64_t n, int d, int dtype, int P, int cus, AssignParams
                    : dtype == kF16 ? rows_per_wg<kF16>(p.KB) : rows_per_wg<kBF16>(p.KB);
   // Two workgroups per CU run at once.  Fewer than four such rounds of row
   // blocks leave CUs idle (or a last round nearly empty): the centroids are
-  // then split over workgroups too, at least four 64-centroid groups each.
+  // then split over workgroups too, at least one 64-centroid group each.
   const int64_t wgs = (n + rows - 1) / rows;
   int64_t splits = wgs >= 8LL * cus ? 1 : (8LL * cus + wgs - 1) / wgs;
   const int64_t most = ppad / kAPad;

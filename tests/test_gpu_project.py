@@ -1,6 +1,6 @@
 """The transform of datastore-sized batches on the 16-bit matrix cores (from
-about 2^30 multiply-adds on) at the edges of its variants: each number of
-column tiles, several column groups, ragged rows, dims (with 16- and 4-byte
+about 2^30 multiply-adds on) in every instance of its kernel (column tiles, copy
+width, whole rows or partial sums) and at their edges: several column groups, ragged rows, dims (with 16- and 4-byte
 copies) and columns, D split or not, whole rows normalised in the kernel or
 after it.  Bound: the fp32 bound of test_gpu_transform, per element; rows that
 the split into bf16 parts does not hold come out as the fp32 kernels give them
@@ -44,6 +44,21 @@ def test_project_split(gpu_lib, M, D, l):
         tol = bound(x[r:r + step], mean, var, W, 1e-5, want)
         assert np.all(err <= tol), (float(err.max()), float((err / tol).max()))
     assert not got[M // 2].any()
+
+
+@pytest.mark.parametrize("whole", [True, False], ids=["whole", "split"])
+@pytest.mark.parametrize("vec", [True, False], ids=["16B", "4B"])
+@pytest.mark.parametrize("nt", range(1, 9))
+def test_every_instance(gpu_lib, nt, vec, whole):
+    """Each instance of the kernel once: nt tiles of 16 columns (a few columns
+    short), rows copied 16 or 4 bytes a lane, rows normalised in the kernel (four
+    blocks of dims, too few to split) or partial sums of slices (32 blocks, fewer
+    row blocks than half the CUs)."""
+    l = 16 * nt - nt % 3
+    D = (128 if whole else 1024) - (0 if vec else 1)
+    even = D % 4 == 0 and l % 64 == 0  # twice the work before this path is taken
+    M = -(-(2 ** 30 if even else 2 ** 29) // (D * l))
+    test_project_split(gpu_lib, M, D, l)
 
 
 @pytest.mark.parametrize("M,D,l", [(66000, 128, 128), (1030, 4096, 256)])
