@@ -31,6 +31,7 @@
 // -1, and dresd_kmeans_assign then computes the marked rows.
 #include "dresd_device.h"
 #include "dresd_ops.h"
+#include "dresd_split.h"
 
 namespace dresd {
 
@@ -40,8 +41,6 @@ constexpr int kAT = 16;          // centroids per tile
 constexpr int kAPad = 64;        // centroids are padded to whole groups of 64
 constexpr int kAWaves = 4;
 
-typedef uint16_t us8 __attribute__((ext_vector_type(8)));
-
 template <int DT>
 __device__ __forceinline__ f4 mfma16(u4 a, u4 b, f4 acc) {
   if constexpr (DT == kF16)
@@ -50,28 +49,6 @@ __device__ __forceinline__ f4 mfma16(u4 a, u4 b, f4 acc) {
   else
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8, a),
                                                    __builtin_bit_cast(b8, b), acc, 0, 0, 0);
-}
-
-// Three 16-bit parts of x (f16 when F16, else bf16), each the rounded rest.
-template <bool F16>
-__device__ __forceinline__ void split3(float x, uint16_t &a, uint16_t &b, uint16_t &c) {
-  if constexpr (F16) {
-    const _Float16 h = (_Float16)x;
-    const float r1 = x - (float)h;
-    const _Float16 m = (_Float16)r1;
-    const _Float16 l = (_Float16)(r1 - (float)m);
-    a = __builtin_bit_cast(uint16_t, h);
-    b = __builtin_bit_cast(uint16_t, m);
-    c = __builtin_bit_cast(uint16_t, l);
-  } else {
-    const __bf16 h = (__bf16)x;
-    const float r1 = x - (float)h;
-    const __bf16 m = (__bf16)r1;
-    const __bf16 l = (__bf16)(r1 - (float)m);
-    a = __builtin_bit_cast(uint16_t, h);
-    b = __builtin_bit_cast(uint16_t, m);
-    c = __builtin_bit_cast(uint16_t, l);
-  }
 }
 
 // Centroid operands: one workgroup per tile of 16 centroids, 16 threads per
@@ -132,16 +109,6 @@ __global__ void __launch_bounds__(256) dresd_assign_operand(AssignParams p) {
   if (p.packed)
     for (int64_t i = (int64_t)tile * 256 + tid; i < p.n; i += (int64_t)gridDim.x * 256)
       p.packed[i] = 0ull;
-}
-
-// Copy one 1 KiB block (16 bytes per lane) into LDS; see copy1_to_lds.
-__device__ __forceinline__ void copy_block_to_lds(const void *src, uint32_t voff, uint32_t lds) {
-  asm volatile(
-      "s_mov_b32 m0, %2\n\t"
-      "global_load_lds_dwordx4 %0, %1"
-      :
-      : "v"(voff), "s"(src), "s"(lds)
-      : "memory");
 }
 
 // Shape of a variant: KB blocks of 32 dims; XP parts per row (1, or 3 for
@@ -270,7 +237,7 @@ __global__ void __launch_bounds__(256, 2) dresd_assign_split(AssignParams p) {
     for (int i = 0; i < CPW; ++i) {
       const int b = wv * CPW + i;
       const int bb = b < Sh::NB ? b : Sh::NB - 1;
-      copy_block_to_lds(src, (uint32_t)(bb * kBlockBytes + lane * 16),
+      copy16_to_lds(src, (uint32_t)(bb * kBlockBytes + lane * 16),
                         base + (uint32_t)(b * kBlockBytes));
     }
     // (64 floats from the stage's first centroid; the array ends 64 past ppad)

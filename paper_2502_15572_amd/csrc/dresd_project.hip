@@ -33,26 +33,14 @@
 // of its rows after another 3.4 / 21 / 65 ms).
 #include "dresd_device.h"
 #include "dresd_ops.h"
+#include "dresd_split.h"
 
 namespace dresd {
 
 namespace {
 
-typedef uint16_t us8 __attribute__((ext_vector_type(8)));
-
 constexpr int kPWaves = 8, kPRows = 32 * kPWaves;  // rows per workgroup
 constexpr int kXWave = 32 * 128 + 256;  // a wave's rows of a 32-dim block, its means and factors
-
-// Three bf16 parts of x, each the rounded rest.
-__device__ __forceinline__ void split3(float x, uint16_t &a, uint16_t &b, uint16_t &c) {
-  const __bf16 h = (__bf16)x;
-  const float r1 = x - (float)h;
-  const __bf16 m = (__bf16)r1;
-  const __bf16 l = (__bf16)(r1 - (float)m);
-  a = __builtin_bit_cast(uint16_t, h);
-  b = __builtin_bit_cast(uint16_t, m);
-  c = __builtin_bit_cast(uint16_t, l);
-}
 
 // Weight operands [group][block of 32 dims][tile][part][64 lanes] x 16 bytes
 // (lane (g, m): column m of the tile, dims 8 g .. + 8; zero past D and l), and
@@ -75,7 +63,7 @@ __global__ void __launch_bounds__(256) dresd_project_operand(ProjectParams p) {
     const float x = (k < p.t.D && c < p.t.l) ? p.t.W[(int64_t)k * p.t.l + c] : 0.f;
     big = fabsf(x) <= big ? big : x == x ? fabsf(x) : __builtin_inff();
     uint16_t a, b, l;
-    split3(x, a, b, l);
+    split3<false>(x, a, b, l);
     part[0][e] = a;
     part[1][e] = b;
     part[2][e] = l;
@@ -98,16 +86,7 @@ __global__ void __launch_bounds__(256) dresd_project_operand(ProjectParams p) {
   }
 }
 
-// Copies into LDS from base + this lane's offset, 16 or 4 bytes per lane (see
-// copy1_to_lds); nt: streamed past the cache.
-__device__ __forceinline__ void copy16_to_lds(const void *base, uint32_t off, uint32_t lds) {
-  asm volatile(
-      "s_mov_b32 m0, %2\n\t"
-      "global_load_lds_dwordx4 %0, %1"
-      :
-      : "v"(off), "s"(base), "s"(lds)
-      : "memory");
-}
+// As copy16_to_lds, 16 or 4 bytes per lane, streamed past the cache.
 __device__ __forceinline__ void copy16_nt_to_lds(const void *base, uint32_t off, uint32_t lds) {
   asm volatile(
       "s_mov_b32 m0, %2\n\t"
@@ -227,7 +206,7 @@ __global__ void __launch_bounds__(64 * kPWaves, 2) dresd_project_split(ProjectPa
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         uint16_t pa, pb, pc;
-        split3((v[e] - mu[e]) * inv[e], pa, pb, pc);
+        split3<false>((v[e] - mu[e]) * inv[e], pa, pb, pc);
         part[0][e] = pa;
         part[1][e] = pb;
         part[2][e] = pc;

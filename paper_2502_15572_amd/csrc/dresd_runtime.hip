@@ -579,78 +579,78 @@ dresd_status make_plan(dresd_index *ix, int B, int k, Plan &pl, bool filt = fals
     pl.lds = scan_lds(bmax * pl.terms, ix->KB, pl.qt * pl.qpt, pl.CL, pl.C);
   }
   if (!pl.small) {
-  const int bmax = pl.bmax;
-  const int ngr = (int)ceil_div(B, bmax);
-  // The single-tile scan serves several groups per launch; launch sizes
-  // differ by at most one query and each splits into groups of <= bmax.
-  const int per = (pl.mq || pl.tc)
-                      ? 1
-                      : std::max(1, std::min({ngr, kGroupsPerLaunch, (int)(kMaxGroup / bmax)}));
-  pl.B = B;
-  pl.nl = (int)ceil_div(ngr, per);
-  pl.bl = (int)ceil_div(B, pl.nl);  // launch sizes differ by at most one query
-  if (per > 1 && pl.qt == 1) {
-    pl.kmain = scan_kernel(ix->dtype, pl.qt, pl.terms, true, true);
-    pl.ksample = scan_kernel(ix->dtype, pl.qt, pl.terms, false, true);
-  }
-  if (!pl.kmain || !pl.ksample) return fail(DRESD_EUNSUPPORTED, "no scan kernel for this shape");
-  if (!pl.tc) pl.lds_s = pl.lds;
-  if (pl.lds > ix->lds_max) return fail(DRESD_EUNSUPPORTED, "scan state does not fit in LDS");
-  int occ = std::min(occupancy(ix, pl.kmain, pl.lds, keep_cache, threads_of(pl, true)),
-                     occupancy(ix, pl.ksample, pl.lds_s, keep_cache, threads_of(pl, false)));
-  // At most four workgroups per CU (few enough lists for the merge to keep
-  // their best keys in LDS); one where fewer, longer HBM streams measured
-  // faster: the single-tile scan with one query tile, and the shared-key
-  // scan over 32-block (1 KiB-row) key tiles.
-  const bool one_per_cu = pl.tc || (pl.mq ? ix->KB >= 32 : pl.qt == 1);
-  pl.wg_max = ix->cus * std::min(occ, one_per_cu ? kMaxTileWgPerCu : kMaxScanWgPerCu);
-  // lists per query from each workgroup (at most kMergeLists in all): one per
-  // wave, one for the shared-key scan, and one per key group of waves for
-  // the tiled contraction (of the pass kind with more)
-  const int lists_per_wg = pl.mq ? 1 : pl.tc ? std::max(pl.nk_main, pl.nk_sample)
-                                             : kScanThreads / kWaveSize;
-  pl.wg_max = std::min(pl.wg_max, kMergeLists / lists_per_wg);
-  pl.G_max = pl.wg_max * lists_per_wg;
-  // Small batches (B <= 8): every wave keeps its own running top-k and sorts
-  // it at the end; the merge then prunes with the best per-wave k-th key.
-  // Batches past 8 queries, and smaller ones with k >= 16 and B * k >= 64
-  // (query, rank) pairs (measured: +5% at 5-8 queries, k = 16; +28-60% at
-  // 4-8 queries, k = 100; fewer (query, rank) pairs leave the main pass few
-  // candidates anyway), first set per-query thresholds from sampled passes
-  // over tiles
-  // j*P, sparsest first (kept when they hold at least 4k rows and are at
-  // most a quarter of the tiles).  A pass at stride P leaves about P*k
-  // candidates per query for the next one, so batches with many
-  // (query, rank) pairs add a denser level: its extra sampled scan costs less
-  // than the candidates it removes from the full pass.  The single-tile
-  // scan, whose waves cut their lists early on their own, does best with
-  // one pass at stride 256 (measured: 1.5-4% faster than 4096, 64 at
-  // 1-4 queries and at d = 4096 groups; the shared-key scan is faster with
-  // the two levels).
-  pl.sort_lists = B <= 8;
-  if (!pl.sort_lists || (k >= 16 && (int64_t)B * k >= 64)) {
-    const bool dense = (int64_t)B * k >= 8192;
-    // The tiled contraction's passes take about as long at stride 64 as
-    // at 256 (a K loop over every column per panel, whatever the panel
-    // count): one pass, at the sparsest of 64, 16 and 4 that lists enough
-    // tiles.
-    const std::vector<int64_t> ladder =
-        pl.tc    ? std::vector<int64_t>{64, 16, 4}
-        : dense  ? std::vector<int64_t>{4096, 256, 16}
-        : pl.mq  ? std::vector<int64_t>{4096, 64}
-                 : std::vector<int64_t>{256};
-    for (int64_t P : ladder) {
-      int64_t nv = ceil_div(ix->T, P);
-      // the tiled contraction's sampled pass lists one key per tile and query
-      const int64_t rows = pl.tc ? nv : nv * kTileRows;
-      if (rows >= 4 * (int64_t)k && ix->T >= 4 * P) {
-        pl.strides[pl.npass++] = P;
-        if (pl.tc) break;
-      }
+    const int bmax = pl.bmax;
+    const int ngr = (int)ceil_div(B, bmax);
+    // The single-tile scan serves several groups per launch; launch sizes
+    // differ by at most one query and each splits into groups of <= bmax.
+    const int per = (pl.mq || pl.tc)
+                        ? 1
+                        : std::max(1, std::min({ngr, kGroupsPerLaunch, (int)(kMaxGroup / bmax)}));
+    pl.B = B;
+    pl.nl = (int)ceil_div(ngr, per);
+    pl.bl = (int)ceil_div(B, pl.nl);  // launch sizes differ by at most one query
+    if (per > 1 && pl.qt == 1) {
+      pl.kmain = scan_kernel(ix->dtype, pl.qt, pl.terms, true, true);
+      pl.ksample = scan_kernel(ix->dtype, pl.qt, pl.terms, false, true);
     }
-    for (int i = 0; i + 1 < pl.npass; ++i)
-      pl.spec[i] = spec_rank(k, pl.strides[i] / pl.strides[i + 1]);
-  }
+    if (!pl.kmain || !pl.ksample) return fail(DRESD_EUNSUPPORTED, "no scan kernel for this shape");
+    if (!pl.tc) pl.lds_s = pl.lds;
+    if (pl.lds > ix->lds_max) return fail(DRESD_EUNSUPPORTED, "scan state does not fit in LDS");
+    int occ = std::min(occupancy(ix, pl.kmain, pl.lds, keep_cache, threads_of(pl, true)),
+                       occupancy(ix, pl.ksample, pl.lds_s, keep_cache, threads_of(pl, false)));
+    // At most four workgroups per CU (few enough lists for the merge to keep
+    // their best keys in LDS); one where fewer, longer HBM streams measured
+    // faster: the single-tile scan with one query tile, and the shared-key
+    // scan over 32-block (1 KiB-row) key tiles.
+    const bool one_per_cu = pl.tc || (pl.mq ? ix->KB >= 32 : pl.qt == 1);
+    pl.wg_max = ix->cus * std::min(occ, one_per_cu ? kMaxTileWgPerCu : kMaxScanWgPerCu);
+    // lists per query from each workgroup (at most kMergeLists in all): one per
+    // wave, one for the shared-key scan, and one per key group of waves for
+    // the tiled contraction (of the pass kind with more)
+    const int lists_per_wg = pl.mq ? 1 : pl.tc ? std::max(pl.nk_main, pl.nk_sample)
+                                               : kScanThreads / kWaveSize;
+    pl.wg_max = std::min(pl.wg_max, kMergeLists / lists_per_wg);
+    pl.G_max = pl.wg_max * lists_per_wg;
+    // Small batches (B <= 8): every wave keeps its own running top-k and sorts
+    // it at the end; the merge then prunes with the best per-wave k-th key.
+    // Batches past 8 queries, and smaller ones with k >= 16 and B * k >= 64
+    // (query, rank) pairs (measured: +5% at 5-8 queries, k = 16; +28-60% at
+    // 4-8 queries, k = 100; fewer (query, rank) pairs leave the main pass few
+    // candidates anyway), first set per-query thresholds from sampled passes
+    // over tiles
+    // j*P, sparsest first (kept when they hold at least 4k rows and are at
+    // most a quarter of the tiles).  A pass at stride P leaves about P*k
+    // candidates per query for the next one, so batches with many
+    // (query, rank) pairs add a denser level: its extra sampled scan costs less
+    // than the candidates it removes from the full pass.  The single-tile
+    // scan, whose waves cut their lists early on their own, does best with
+    // one pass at stride 256 (measured: 1.5-4% faster than 4096, 64 at
+    // 1-4 queries and at d = 4096 groups; the shared-key scan is faster with
+    // the two levels).
+    pl.sort_lists = B <= 8;
+    if (!pl.sort_lists || (k >= 16 && (int64_t)B * k >= 64)) {
+      const bool dense = (int64_t)B * k >= 8192;
+      // The tiled contraction's passes take about as long at stride 64 as
+      // at 256 (a K loop over every column per panel, whatever the panel
+      // count): one pass, at the sparsest of 64, 16 and 4 that lists enough
+      // tiles.
+      const std::vector<int64_t> ladder =
+          pl.tc    ? std::vector<int64_t>{64, 16, 4}
+          : dense  ? std::vector<int64_t>{4096, 256, 16}
+          : pl.mq  ? std::vector<int64_t>{4096, 64}
+                   : std::vector<int64_t>{256};
+      for (int64_t P : ladder) {
+        int64_t nv = ceil_div(ix->T, P);
+        // the tiled contraction's sampled pass lists one key per tile and query
+        const int64_t rows = pl.tc ? nv : nv * kTileRows;
+        if (rows >= 4 * (int64_t)k && ix->T >= 4 * P) {
+          pl.strides[pl.npass++] = P;
+          if (pl.tc) break;
+        }
+      }
+      for (int i = 0; i + 1 < pl.npass; ++i)
+        pl.spec[i] = spec_rank(k, pl.strides[i] / pl.strides[i + 1]);
+    }
   }
   // Lists end with at most k keys each (C where whole tiles are listed), so a
   // query never has more than G_max times that many merge candidates.
