@@ -494,13 +494,19 @@ dresd_status make_plan(dresd_index *ix, int B, int k, Plan &pl, bool filt = fals
   // scan: 16,384 x 256 fp32 at B = 1 / 8 / 128 16.3 / 17.7 / 43.6 us (18.1 /
   // 28.9 / 167), 65,536 x 128 f16 at B = 1 15.6 us (21.9), 262,144 x 128 f16
   // 26.5 us (35.7).  Past 128 MiB of keys long streams win (262,144 x 1,024
-  // bf16 122 us against 101), with the next-token filter, which leaves one
-  // query few candidates, past 32 MiB (262,144 x 128 f16 28.2 against 27.5).
+  // bf16 122 us against 101).  With the next-token filter, which leaves one
+  // query few candidates to stage, the two are level from 32 MiB on (nine shapes
+  // of 40,000 x 1,024 to 262,144 x 128, k of 1 to 63, all key types: 20-42 us, each
+  // ahead by up to a quarter in some runs) and the shorter workspace decides,
+  // until k brings the single-tile scan a sampled pass (262,144 x 128 f16, k =
+  // 100: 23-30 us against 44; 131,072 x 256 fp32 34 against 52).
   // Waves of 16 blocks or fewer take several tiles while that leaves more
   // lists than CUs.
+  // (batches past eight queries, and smaller ones with many (query, rank) pairs)
+  const bool sampled = B > 8 || (k >= 16 && (int64_t)B * k >= 64);
   if (small_ok && !pl.tc && !(mq_type && mq_kb && (qt_all >= 2 || pl.terms < 4)) &&
       (ix->dtype == kF32 || pl.terms == 4) && ix->KB <= 32 && ix->T <= 4 * kMergeLists &&
-      ix->T * ix->KB <= (filt && B == 1 ? kSmallBlocks / 4 : kSmallBlocks) &&
+      ix->T * ix->KB <= (filt && B == 1 && !sampled ? kSmallBlocks / 4 : kSmallBlocks) &&
       (int64_t)B * ix->T <= kSmallTiles) {
     int tpw = 1;
     for (int64_t g = ix->T;
@@ -628,7 +634,7 @@ dresd_status make_plan(dresd_index *ix, int B, int k, Plan &pl, bool filt = fals
     // 1-4 queries and at d = 4096 groups; the shared-key scan is faster with
     // the two levels).
     pl.sort_lists = B <= 8;
-    if (!pl.sort_lists || (k >= 16 && (int64_t)B * k >= 64)) {
+    if (sampled) {
       const bool dense = (int64_t)B * k >= 8192;
       // The tiled contraction's passes take about as long at stride 64 as
       // at 256 (a K loop over every column per panel, whatever the panel

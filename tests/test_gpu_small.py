@@ -28,6 +28,8 @@ CASES = [
     ("f16", 16384, 128, 4, 100),
     ("f16", 40003, 100, 1, 16),     # ragged dims, two tiles per wave
     ("f16", 9999, 1024, 3, 7),
+    ("f16", 140001, 128, 1, 100),   # past 32 MiB: with the filter as well, from 64 ranks on
+    ("f16", 140001, 128, 1, 63),
     ("bf16", 20011, 33, 2, 50),
     ("bf16", 2047, 700, 4, 300),
 ]
