@@ -10,6 +10,8 @@
 // dresd_merge.hip.
 #include "dresd_scan_common.h"
 
+#include <type_traits>
+
 namespace dresd {
 
 // ------------------------------------------------------------------ scan ---
@@ -572,6 +574,51 @@ __device__ void parts_segments(const int64_t *probes, const int32_t *part_tile, 
   __syncthreads();
 }
 
+// Scores of the slots of NT tiles (base: this lane's chunk of each one's first
+// block): lane (g, m) gets that of row m of tile g (of the first tile where g is
+// past them).  operand(kb) gives the query's operand of block kb, its parts
+// repeated in all four row groups.  16 blocks (12 of three tiles) are in flight.
+template <int DT, int CPQ, int NT, class Operand>
+__device__ __forceinline__ float few_scores(const u4 *const *base, int KB, int g,
+                                            const Operand &operand) {
+  constexpr int U = NT == 3 ? 4 : 16 / NT;
+  f4 acc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+  int kb = 0;
+  auto step = [&](auto blocks) {
+    constexpr int N = decltype(blocks)::value;
+    u4 blk[N][NT];
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) blk[u][t] = __builtin_nontemporal_load(base[t] + (kb + u) * 64);
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const u4 a = operand(kb + u);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[t] = Mfma<DT>::run(a, blk[u][t], acc[t]);
+    }
+    kb += N;
+  };
+  while (kb + U <= KB) step(std::integral_constant<int, U>());
+  if constexpr (U > 4)
+    while (kb + 4 <= KB) step(std::integral_constant<int, 4>());
+  while (kb < KB) step(std::integral_constant<int, 1>());
+  f4 s = acc[0];
+#pragma unroll
+  for (int t = 1; t < NT; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s[i] = g == t ? acc[t][i] : s[i];
+  float sc = s[0];
+  if (CPQ == 4) {
+    const float s1 = (DT == kF16) ? (1.0f / 2048.0f) : 1.0f;
+    const float s2 = (DT == kF16) ? (1.0f / 4194304.0f) : 1.0f;
+    sc = (sc + s[1] * s1) + s[2] * s2;
+  }
+  return sc;
+}
+
 // Partitioned search whose waves' lists hold every slot of their tiles (at
 // most C / 16 tiles each): no stage, threshold or cut.  Short streams are bounded
 // by latency, so a wave takes four tiles at a time with everything it reads for
@@ -626,42 +673,11 @@ __device__ __forceinline__ void scan_few_tiles(const ScanParams &p, int gw, cons
     for (int t = 0; t < 4; ++t)
       base[t] = static_cast<const u4 *>(p.data) +
                 (int64_t)__builtin_amdgcn_readlane(tile, t * 16) * KB * 64 + lane;
-    f4 acc[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
-    int kb = 0;
-    for (; kb + 4 <= KB; kb += 4) {
-      u4 blk[4][4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) blk[u][t] = __builtin_nontemporal_load(base[t] + (kb + u) * 64);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const u4 a = operand(kb + u);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) acc[t] = Mfma<DT>::run(a, blk[u][t], acc[t]);
-      }
-    }
-    for (; kb < KB; ++kb) {
-      u4 blk[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) blk[t] = __builtin_nontemporal_load(base[t] + kb * 64);
-      const u4 a = operand(kb);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) acc[t] = Mfma<DT>::run(a, blk[t], acc[t]);
-    }
-    f4 s = acc[0];
-#pragma unroll
-    for (int t = 1; t < 4; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) s[i] = g == t ? acc[t][i] : s[i];
-    float sc = s[0];
-    if (CPQ == 4) {
-      const float s1 = (DT == kF16) ? (1.0f / 2048.0f) : 1.0f;
-      const float s2 = (DT == kF16) ? (1.0f / 4194304.0f) : 1.0f;
-      sc = (sc + s[1] * s1) + s[2] * s2;
-    }
+    const int left = nt - t0;  // (the same for the whole wave)
+    const float sc = left == 1   ? few_scores<DT, CPQ, 1>(base, KB, g, operand)
+                     : left == 2 ? few_scores<DT, CPQ, 2>(base, KB, g, operand)
+                     : left == 3 ? few_scores<DT, CPQ, 3>(base, KB, g, operand)
+                                 : few_scores<DT, CPQ, 4>(base, KB, g, operand);
     // (a NaN score competes nowhere; key 0 is no candidate)
     const bool in = t0 + g < nt && row != kPadRow && sc == sc &&
                     (!p.ftok || first_tok == *p.next_tok);
@@ -675,7 +691,7 @@ __device__ __forceinline__ void scan_few_tiles(const ScanParams &p, int gw, cons
     best = other > best ? other : best;
   }
   if (lane == 0) {
-    p.lcnt[gw] = best ? (uint32_t)((nt + 3) / 4 * kWaveSize) : 0u;
+    p.lcnt[gw] = best ? (uint32_t)(nt * kTileRows) : 0u;
     p.lfirst[gw] = best;
     p.lkth[gw] = 0;
   }
