@@ -252,3 +252,37 @@ def test_shapes_of_the_whole_tile_scan(gpu_lib, dt, N, d, B, waves):
         assert plan["scan_waves"] == waves and plan["launches"] == 1
         assert plan["sample_passes"] == 0
     ix.close()
+
+
+@pytest.mark.parametrize("dt,d", [("f32", 40), ("f32", 256), ("f32", 340), ("f16", 128),
+                                  ("f16", 680), ("bf16", 512), ("bf16", 700)])
+def test_waves_of_one_to_nine_tiles(gpu_lib, dt, d):
+    """Partitions of 1 to 36 tiles split over four waves: each remainder of a
+    wave's tiles by four, over widths at the edges of the blocks read at a time
+    (3 to 22 blocks; 16, 8 and 4 at a time), against the oracle."""
+    from paper_2502_15572_amd import PartitionedIndex
+    say("waves of one to nine tiles", dt, d)
+    rng = np.random.default_rng(d)
+    tiles = np.array([1, 2, 4, 5, 7, 8, 10, 12, 13, 16, 19, 20, 26, 36])
+    sizes = tiles * 16 - rng.integers(0, 16, tiles.size)
+    P = B = tiles.size
+    a = np.repeat(np.arange(P), sizes).astype(np.int32)
+    N = a.size
+    rng.shuffle(a)
+    keys = as_keys(unit(rng, N, d), dt)
+    cont = rng.integers(0, 9, (N, 2)).astype(np.int32)
+    q = unit(rng, B, d).astype(np.float32)
+    probes = np.arange(P, dtype=np.int32).reshape(B, 1)
+    ix = PartitionedIndex(keys.to(DEV), torch.from_numpy(cont).to(DEV),
+                          torch.from_numpy(unit(rng, P, d).astype(np.float32)).to(DEV),
+                          torch.from_numpy(a).to(DEV))
+    k = 100
+    idx, score, tok = ix.search_probes(torch.from_numpy(q).to(DEV),
+                                       torch.from_numpy(probes).to(DEV), k)
+    torch.cuda.synchronize()
+    kb, kdt = to_numpy_bits(keys)
+    o_idx, o_score, _, o_next = oracle.topk_partitioned(kb, kdt, q, k, a, P, probes, cont)
+    check_batch(idx.cpu().numpy(), score.cpu().numpy(), tok.cpu().numpy(), o_idx, o_score, o_next,
+                lambda b, rows: oracle.score_rows(kb, kdt, q[b], rows), N, cont, 1e-5,
+                admitted_b=lambda b, rows: a[rows] == b)
+    ix.close()
